@@ -690,6 +690,42 @@ __device__ __forceinline__ double2 fold_bin_single(const FftView &fv, const doub
     return ok ? z : make_double2(0.0, 0.0);
 }
 
+// All bins of a short ring at once, 0 <= k < nb <= FOLD_MAX, into LDS: P threads
+// (a power of two, lanes of one wavefront) per bin take every Pth term of it and
+// add their sums in a fixed tree; rings y of F row Frow and, where yb >= 0, i times
+// the bins of a second ring.  A short ring has few bins and many terms (a HEALPix
+// polar ring of 4 pixels folds 2 mv / 4 of them onto each, mv >= 100): one thread per
+// bin, each term a dependent load, took 68 us of the 343 us pair of one spin-2
+// transform at N_side 128, this takes 17.  Up to 128 bins: there 1024 threads give
+// each at least 8 terms at a time; longer rings have fewer terms per bin than lanes.
+constexpr int FOLD_MAX = 128;
+
+__device__ __forceinline__ void fold_short(const FftView &fv, double2 *bins, const double2 *Fa, int ya, int mva,
+                                           const double2 *Fb, int yb, int mvb, int N, int nb)
+{
+    const int T = (int)blockDim.x;
+    int P = 64;
+    while (P > 1 && P * nb > T) P >>= 1;
+    const int j = (int)threadIdx.x % P;
+    for (int k0 = (int)threadIdx.x / P; k0 < (nb + T / P - 1) / (T / P) * (T / P); k0 += T / P) {
+        const int k = min(k0, nb - 1);
+        double2 s = make_double2(0.0, 0.0);
+        auto ring = [&](const double2 *F, int y, int mv, bool second) {
+            auto add = [&](double2 t) { s = cadd(s, second ? make_double2(-t.y, t.x) : t); };
+            for (int m = k + N * j; m <= mv; m += N * P) add(rotate(fv, F[m], y, m));
+            for (int m = N - k + N * j; m <= mv; m += N * P) add(cconj(rotate(fv, F[m], y, m)));
+        };
+        ring(Fa, ya, mva, false);
+        if (yb >= 0) ring(Fb, yb, mvb, true);
+        for (int o = P >> 1; o > 0; o >>= 1) {
+            s.x += __shfl_xor(s.x, o);
+            s.y += __shfl_xor(s.y, o);
+        }
+        if (j == 0 && k0 < nb) bins[k] = s;
+    }
+    __syncthreads();
+}
+
 // Rader's algorithm for a prime length L with smooth L-1: with a generator g
 // of the multiplicative group mod L, a_p = x_{g^p} and b_q = w^{g^{-q}}
 // (w = e^{-+2 pi i / L}), X_{g^{-q}} = x_0 + (a (*) b)_q, a cyclic convolution of
@@ -782,6 +818,7 @@ __global__ __launch_bounds__(1024) void k_ring_synth(FftView fv, const int *__re
                                                     double *__restrict__ map, int use_weights)
 {
     extern __shared__ double2 buf[];
+    __shared__ double2 bins[MODE == KMODE_LDS ? FOLD_MAX : 1];   // folded spectrum of a short ring
     const FftRow row = fv.rows[rowlist[blockIdx.x]];
     const int tc = blockIdx.y;   // transform * ncomp + component
     const FftLen d = fv.lens[row.len];
@@ -817,8 +854,14 @@ __global__ __launch_bounds__(1024) void k_ring_synth(FftView fv, const int *__re
             return make_double2(A.x - B.y, A.y + B.x);
         };
         SpecRead<MODE, lds_pad<MODE, POW2>()> out;
-        if (N > 2 * max(mva, mvb)) out = ring_transform<MODE, POW2>(buf, fv, d, false, zin1);
-        else out = ring_transform<MODE, POW2>(buf, fv, d, false, zin);
+        if (N > 2 * max(mva, mvb)) {
+            out = ring_transform<MODE, POW2>(buf, fv, d, false, zin1);
+        } else if (MODE == KMODE_LDS && N <= FOLD_MAX) {
+            fold_short(fv, bins, Fa, row.ya, mva, Fbs, row.yb, mvb, N, N);
+            out = ring_transform<MODE, POW2>(buf, fv, d, false, [&](int k) { return bins[k]; });
+        } else {
+            out = ring_transform<MODE, POW2>(buf, fv, d, false, zin);
+        }
         const int64_t oa = fv.ofs[row.ya], ob = row.yb >= 0 ? fv.ofs[row.yb] : oa;
         const bool hasb = row.yb >= 0;
         batched_loop<false, LOOP_U>(N, out, [&](int x, double2 z) {
@@ -842,8 +885,15 @@ __global__ __launch_bounds__(1024) void k_ring_synth(FftView fv, const int *__re
                         cconj(fold_bin_single(fv, Fa, row.ya, N, mva, h - k)), k);
         };
         SpecRead<MODE, lds_pad<MODE, POW2>()> out;
-        if (N > 2 * mva) out = ring_transform<MODE, POW2>(buf, fv, d, false, zin1);
-        else out = ring_transform<MODE, POW2>(buf, fv, d, false, zin);
+        if (N > 2 * mva) {
+            out = ring_transform<MODE, POW2>(buf, fv, d, false, zin1);
+        } else if (MODE == KMODE_LDS && h < FOLD_MAX) {
+            fold_short(fv, bins, Fa, row.ya, mva, Fa, -1, -1, N, h + 1);
+            out = ring_transform<MODE, POW2>(buf, fv, d, false,
+                                             [&](int k) { return pack(bins[k], cconj(bins[h - k]), k); });
+        } else {
+            out = ring_transform<MODE, POW2>(buf, fv, d, false, zin);
+        }
         const int64_t oa = fv.ofs[row.ya];
         batched_loop<false, LOOP_U>(h, out, [&](int n, double2 z) {
             mp[oa + (int64_t)(2 * n) * fv.stride] = wa * z.x;
