@@ -19,6 +19,14 @@ using namespace sht;
 
 namespace {
 
+// Plans whose Legendre steps the persistent queues do not run: those on the
+// vector-unit kernels and those with a scalar part.
+bool own_launches(const Plan &p) { return p.tune.valu || p.eq; }
+bool own_launches(const Batch &b)
+{
+    return std::any_of(b.plans.begin(), b.plans.end(), [](const Plan *p) { return own_launches(*p); });
+}
+
 void batch_free(Batch *b)
 {
     for (int d = 0; d < NUM_DIRECTIONS; ++d)
@@ -87,7 +95,7 @@ void synth_queue(Batch &b, std::vector<BatchSynItem> &q)
     std::vector<Block> blocks;
     for (int pi = 0; pi < (int)b.plans.size(); ++pi) {
         const Plan &p = *b.plans[pi];
-        const int jpg = p.tune.synth_ncb * 16 / cpj;
+        const int jpg = b.syn_ncb * 16 / cpj;
         const int MB = std::max(1, p.tune.synth_mblock);
         auto lrange = [&](int m) { return (double)(p.lmax + 1 - std::max(m, p.spin)); };
         const bool pairs = b.queue_order == SHT_QUEUE_MPAIRS;
@@ -96,8 +104,11 @@ void synth_queue(Batch &b, std::vector<BatchSynItem> &q)
             Block blk;
             for (int m = m0; m <= std::min(mend, m0 + MB - 1); ++m) {
                 const int m2 = pairs ? p.mmax - m : -1;
-                for (int t = 0; t < p.ntiles; ++t) {
-                    const bool a1 = p.tile_mlim[t] >= m, a2 = pairs && m2 != m && p.tile_mlim[t] >= m2;
+                const int step = synth_tile_step(p);
+                for (int t = 0; t < p.ntiles; t += step) {
+                    int lim = -1;
+                    for (int u = t; u < std::min(p.ntiles, t + step); ++u) lim = std::max(lim, p.tile_mlim[u]);
+                    const bool a1 = lim >= m, a2 = pairs && m2 != m && lim >= m2;
                     if (!a1 && !a2) continue;
                     const double c = (a1 ? lrange(m) : 0.0) + (a2 ? lrange(m2) : 0.0);
                     for (int t0 = 0; t0 < p.ntrans; t0 += jpg) {
@@ -153,9 +164,13 @@ int refresh_synth_queue(Batch &b, hipStream_t s, bool force)
     if (b.d_syn) (void)hipDeviceSynchronize();
     const Plan &p0 = *b.plans[0];
     b.syn_ok = true;
-    for (const Plan *p : b.plans)
-        if (p->tune.valu || p->tune.synth_ncb != p0.tune.synth_ncb || p->flush_chunks != p0.flush_chunks)
-            b.syn_ok = false;
+    b.syn_ncb = p0.tune.synth_ncb;
+    for (const Plan *p : b.plans) {
+        // (the two-step kernels' results do not depend on the column blocks)
+        if (two_step(*p)) b.syn_ncb = std::max(b.syn_ncb, p->tune.synth_ncb);
+        else if (p->tune.synth_ncb != b.syn_ncb) b.syn_ok = false;
+        if (own_launches(*p) || p->flush_chunks != p0.flush_chunks) b.syn_ok = false;
+    }
     dev_free(b.d_syn);
     b.d_syn = nullptr;
     b.nsyn = 0;
@@ -165,7 +180,6 @@ int refresh_synth_queue(Batch &b, hipStream_t s, bool force)
         b.syn_gen = gen;
         return SHT_OK;
     }
-    b.syn_ncb = p0.tune.synth_ncb;
     b.syn_flush = p0.flush_chunks;
     b.syn_groups = synth_batch_groups(b.spin, b.syn_ncb, b.precision == SHT_FP32_MFMA, b.device);
     std::vector<BatchSynItem> q;
@@ -239,6 +253,15 @@ int plan_legendre_synth(Batch &b, int i, int direction, const double *in, double
     return launch_legendre_synth(p, a, phase, deriv_direction(direction), s);
 }
 
+// Legendre analysis of plan i by its own launches (with the real-harmonics conversion).
+int plan_legendre_anal(Batch &b, int i, int direction, const double *phase, double *out, hipStream_t s)
+{
+    Plan &p = *b.plans[i];
+    int rc = launch_legendre_anal(p, phase, out, anal_mode(direction, b.real_h), s);
+    if (!rc && b.real_h) rc = launch_real_harm(p, out, out, deriv_direction(direction) ? 1 : p.ncomp, false, s);
+    return rc;
+}
+
 // Persistent Legendre analysis over all plans, then the real-harmonics conversion.
 int batch_legendre_anal(Batch &b, int direction, const double *const *phase, double *const *out, hipStream_t s)
 {
@@ -250,16 +273,12 @@ int batch_legendre_anal(Batch &b, int direction, const double *const *phase, dou
         ptrs.out[i] = out[i];
     }
     int rc;
-    bool valu = false;
-    for (const Plan *p : b.plans) valu = valu || p->tune.valu;
-    if (valu) {
-        // plans on the vector-unit path: each plan's own analysis launch (the
-        // persistent queue runs the matrix-core kernels), same results as the plans
+    if (own_launches(b)) {   // each plan's own analysis launches, same results as the plans
         for (int i = 0; i < np; ++i)
-            if ((rc = launch_legendre_anal(*b.plans[i], phase[i], out[i], anal_mode(direction, b.real_h), s))) return rc;
-    } else if ((rc = launch_legendre_anal_batch(b, ptrs, anal_mode(direction, b.real_h), s))) {
-        return rc;
+            if ((rc = plan_legendre_anal(b, i, direction, phase[i], out[i], s))) return rc;
+        return SHT_OK;
     }
+    if ((rc = launch_legendre_anal_batch(b, ptrs, anal_mode(direction, b.real_h), s))) return rc;
     if (b.real_h)
         for (int i = 0; i < np; ++i)
             if ((rc = launch_real_harm(*b.plans[i], out[i], out[i], deriv_direction(direction) ? 1 : b.plans[i]->ncomp,
@@ -316,11 +335,15 @@ int batch_enqueue(Batch &b, int direction, const double *const *in, double *cons
         }
         return join_chains(b, s);
     }
-    for (int i = 0; i < np; ++i)
-        if ((rc = launch_ring_anal(*b.plans[i], in[i], b.plans[i]->d_phase, weighted_direction(direction),
-                                   chain_stream(b, i, s))))
+    const bool own = own_launches(b);   // then the whole analysis is a chain per plan
+    for (int i = 0; i < np; ++i) {
+        const hipStream_t cs = chain_stream(b, i, s);
+        if ((rc = launch_ring_anal(*b.plans[i], in[i], b.plans[i]->d_phase, weighted_direction(direction), cs)))
             return rc;
+        if (own && (rc = plan_legendre_anal(b, i, direction, b.plans[i]->d_phase, out[i], cs))) return rc;
+    }
     if ((rc = join_chains(b, s))) return rc;
+    if (own) return SHT_OK;
     std::vector<const double *> ph(np);
     for (int i = 0; i < np; ++i) ph[i] = b.plans[i]->d_phase;
     return batch_legendre_anal(b, direction, ph.data(), out, s);
@@ -468,9 +491,18 @@ int sht_batch_create(int nplans, sht_plan *const *plans, sht_batch **out)
         b->plan_serial.push_back(p->serial);
     }
     b->device = b->plans[0]->device;
-    b->ana_ncb = anal_ncb(b->spin, maxj);
+    b->ana_ncb = two_step(*b->plans[0]) ? anal0_batch_ncb(*b) : anal_ncb(b->spin, maxj);
     b->ana_groups = anal_batch_groups(b->spin, b->ana_ncb, b->precision == SHT_FP32_MFMA, b->device);
     fault_arm();
+    // (the persistent kernels read the matrix-core tables, also of a plan that is
+    // on the vector path now and retuned later)
+    for (Plan *p : b->plans) {
+        const int rc = two_step(*p) ? ensure_tables(*p, false) : SHT_OK;
+        if (rc) {
+            delete b;
+            return rc;
+        }
+    }
     std::vector<LegView> views;
     for (Plan *p : b->plans) views.push_back(make_leg_view(*p));
     int rc;

@@ -14,6 +14,8 @@
 #include <cstring>
 #include <mutex>
 #include <new>
+#include <system_error>
+#include <thread>
 #include <unordered_map>
 #include <utility>
 
@@ -178,13 +180,28 @@ static Geom *geom_from(int nrings, const double *theta, const int64_t *nphi, con
     return g;
 }
 
+static const long double PI_L = 3.14159265358979323846264338327950288L;
+
+// What the double colatitudes of a grid leave of the exact ones, ring by ring
+// (theta itself stays as given out).  A colatitude rounded to double moves the
+// phase of degree l by up to l 2^-53, as much as the recursion's own rounding.
+static int with_residual(int rc, const std::vector<long double> &exact, sht_geom **out)
+{
+    if (rc) return rc;
+    Geom *g = reinterpret_cast<Geom *>(*out);
+    g->theta_lo.resize(g->nrings);
+    for (int i = 0; i < g->nrings; ++i) g->theta_lo[i] = (double)(exact[i] - g->theta[i]);
+    return rc;
+}
+
 // Gauss-Legendre nodes as colatitudes by Newton's method on P_n(cos t) in
 // long double, with weights 2 / ((1 - x^2) P_n'(x)^2).
-static void gauss_legendre(int n, std::vector<double> &theta, std::vector<double> &w)
+static void gauss_legendre(int n, std::vector<double> &theta, std::vector<double> &w, std::vector<long double> &exact)
 {
     theta.resize(n);
     w.resize(n);
-    const long double pi = 3.14159265358979323846264338327950288L;
+    exact.resize(n);
+    const long double pi = PI_L;
     auto legendre = [n](long double c, long double &pn, long double &pn1) {
         long double p0 = 1.0L, p1 = c;
         for (int j = 2; j <= n; ++j) {
@@ -219,16 +236,22 @@ static void gauss_legendre(int n, std::vector<double> &theta, std::vector<double
         w[k - 1] = (double)wk;
         theta[n - k] = M_PI - (double)t;
         w[n - k] = (double)wk;
+        exact[k - 1] = t;
+        exact[n - k] = pi - t;
     }
-    if (n % 2 == 1) theta[n / 2] = 0.5 * M_PI;
+    if (n % 2 == 1) {
+        theta[n / 2] = 0.5 * M_PI;
+        exact[n / 2] = 0.5L * pi;
+    }
 }
 
 // Weights of the rules of sht_geom_ecp on [-1, 1] in x = cos theta, from the
 // closed-form cosine and sine sums of the interpolatory rules (the sums that
 // Waldvogel's FFT method evaluates), in long double.
-static void ecp_rule(int n, int kind, std::vector<double> &th, std::vector<double> &w)
+static void ecp_rule(int n, int kind, std::vector<double> &th, std::vector<double> &w, std::vector<long double> &exact)
 {
-    const long double pi = 3.14159265358979323846264338327950288L;
+    const long double pi = PI_L;
+    exact.assign(n, 0.0L);
     th.assign(n, 0.0);
     w.assign(n, 0.0);
     for (int k = 0; k < n; ++k) {
@@ -256,6 +279,7 @@ static void ecp_rule(int n, int kind, std::vector<double> &th, std::vector<doubl
         }
         th[k] = (double)t;
         w[k] = (double)s;
+        exact[k] = t;
     }
 }
 
@@ -272,28 +296,33 @@ static bool smooth235(int64_t n)
 // other hemisphere"); unmatched rings form single-ring slots.  Slots are
 // ordered from the poles towards the equator (ascending sin theta), so the
 // polar-skip boundary of Sect. 3.3 moves monotonically through the tiles.
-void build_slots(const Geom &g, std::vector<SlotHost> &slots)
+void build_slots(const Geom &g, std::vector<SlotHost> &slots, bool residual)
 {
     std::vector<int> idx(g.nrings);
     for (int i = 0; i < g.nrings; ++i) idx[i] = i;
     std::stable_sort(idx.begin(), idx.end(), [&](int a, int b) { return g.theta[a] < g.theta[b]; });
     const double tol = 8.0 * M_PI * 2.220446049250313e-16;
     slots.clear();
-    auto make = [&](int yn, int ys, double t) {
+    residual = residual && !g.theta_lo.empty();
+    auto lo = [&](int y) { return residual ? (long double)g.theta_lo[y] : 0.0L; };
+    auto make = [&](int yn, int ys, long double t) {
         SlotHost s;
         s.yn = yn;
         s.ys = ys;
-        s.cth = cos(t);
-        s.sth = sin(t);
-        s.chalf = cos(0.5 * t);
-        s.shalf = sin(0.5 * t);
+        const long double cl = cosl(t), sl = sinl(t);
+        s.cth = (double)cl;
+        s.sth = (double)sl;
+        s.chalf = (double)cosl(0.5L * t);
+        s.shalf = (double)sinl(0.5L * t);
+        s.c2 = (double)(cl * cl);
+        s.s2 = (double)(sl * sl);
         slots.push_back(s);
     };
     // a ring beyond the equator is represented by its mirror colatitude
     auto single = [&](int y) {
         double t = g.theta[y];
-        if (t <= 0.5 * M_PI) make(y, -1, t);
-        else make(-1, y, M_PI - t);
+        if (t <= 0.5 * M_PI) make(y, -1, t + lo(y));
+        else make(-1, y, residual ? PI_L - (t + lo(y)) : M_PI - t);
     };
     int i = 0, j = g.nrings - 1;
     while (i <= j) {
@@ -301,7 +330,7 @@ void build_slots(const Geom &g, std::vector<SlotHost> &slots)
         double ti = g.theta[idx[i]], tj = g.theta[idx[j]];
         double d = ti + tj - M_PI;
         if (fabs(d) <= tol && ti <= 0.5 * M_PI) {
-            make(idx[i], idx[j], ti);
+            make(idx[i], idx[j], ti + lo(idx[i]));
             ++i;
             --j;
         } else if (d < 0) {
@@ -331,6 +360,23 @@ int slot_mlim(const PlanShape &ps, const SlotHost &s)
     return -1;
 }
 
+// Fills tables of `total` entries, every m a chain of its own: fill(k, n) does the
+// m = k, k + n, ...  Large tables by several threads.
+template <typename Fill>
+static void fill_by_m(int64_t total, Fill fill)
+{
+    const int nt = total < (1 << 18) ? 1 : (int)std::min(8u, std::max(1u, std::thread::hardware_concurrency()));
+    std::vector<std::thread> others;
+    others.reserve(nt);
+    try {
+        for (int k = 1; k < nt; ++k) others.emplace_back(fill, k, nt);
+    } catch (const std::system_error &) {   // fewer threads than asked for: the rest is done here
+    }
+    fill(0, nt);
+    for (int k = (int)others.size() + 1; k < nt; ++k) fill(k, nt);
+    for (std::thread &t : others) t.join();
+}
+
 // Per-m recursion coefficients for the rescaled recursion used on the GPU.
 //
 // With lambda_l = (-1)^m sqrt((2l+1)/4pi) d^l_{-m,s} (Eq. 10) and the
@@ -356,39 +402,98 @@ void build_coef(const PlanShape &ps, std::vector<Coef4> &coef, std::vector<doubl
     fl.assign((size_t)std::max<int64_t>(total, 1), 0.0);
     int64_t base = 0;
     for (int m = 0; m <= ps.mmax; ++m) {
-        const int l0 = std::max(m, s);
-        ofs[m] = base - l0;
-        const long double mm = m, ss = s;
-        long double f_prev = 1.0L, f_cur = 1.0L;   // f_{l-1}, f_l  (l = l0: f_{l0-1} unused)
-        for (int l = l0; l <= ps.lmax; ++l) {
-            const long double L = l, L1 = l + 1;
-            long double B = sqrtl((L1 * L1 - mm * mm) * (L1 * L1 - ss * ss)) / (L1 * (2 * L + 1));
-            long double P = sqrtl((2 * L + 3) / (2 * L + 1)) / B;
-            long double Q = 0.0L;
-            if (l > l0) {
-                long double A = sqrtl((L * L - mm * mm) * (L * L - ss * ss)) / (L * (2 * L + 1));
-                Q = sqrtl((2 * L + 3) / (2 * L - 1)) * A / B;
-            }
-            long double c = (l > 0) ? mm * ss / (L * L1) : 0.0L;
-            long double f_next = (l == l0) ? 1.0L : Q * f_prev;
-            long double alpha = P * f_cur / f_next;
-            if (l == ps.lmax) alpha = 0.0L;
-            const long double beta = alpha * c;
-            Coef4 e;
-            e.x = (double)alpha;
-            e.y = (double)beta;
-            // t - 2 = (alpha +- beta - 2) - 2 alpha sin^2(t/2): the small part
-            // is formed here in long double, so that near the poles the
-            // recursion sees 1 - cos t at full relative precision
-            e.z = (double)(alpha + beta - 2.0L);
-            e.w = (double)(alpha - beta - 2.0L);
-            coef[(size_t)(base + (l - l0))] = e;
-            fl[(size_t)(base + (l - l0))] = (double)f_cur;
-            f_prev = f_cur;
-            f_cur = f_next;
-        }
-        base += ps.lmax + 1 - l0;
+        ofs[m] = base - std::max(m, s);
+        base += ps.lmax + 1 - std::max(m, s);
     }
+    auto fill = [&](int first, int step) {
+        for (int m = first; m <= ps.mmax; m += step) {
+            const int l0 = std::max(m, s);
+            const int64_t base = ofs[m] + l0;
+            const long double mm = m, ss = s;
+            long double f_prev = 1.0L, f_cur = 1.0L;   // f_{l-1}, f_l  (l = l0: f_{l0-1} unused)
+            for (int l = l0; l <= ps.lmax; ++l) {
+                const long double L = l, L1 = l + 1;
+                long double B = sqrtl((L1 * L1 - mm * mm) * (L1 * L1 - ss * ss)) / (L1 * (2 * L + 1));
+                long double P = sqrtl((2 * L + 3) / (2 * L + 1)) / B;
+                long double Q = 0.0L;
+                if (l > l0) {
+                    long double A = sqrtl((L * L - mm * mm) * (L * L - ss * ss)) / (L * (2 * L + 1));
+                    Q = sqrtl((2 * L + 3) / (2 * L - 1)) * A / B;
+                }
+                long double c = (l > 0) ? mm * ss / (L * L1) : 0.0L;
+                long double f_next = (l == l0) ? 1.0L : Q * f_prev;
+                long double alpha = P * f_cur / f_next;
+                if (l == ps.lmax) alpha = 0.0L;
+                const long double beta = alpha * c;
+                Coef4 e;
+                e.x = (double)alpha;
+                e.y = (double)beta;
+                // t - 2 = (alpha +- beta - 2) - 2 alpha sin^2(t/2): the small part
+                // is formed here in long double, so that near the poles the
+                // recursion sees 1 - cos t at full relative precision
+                e.z = (double)(alpha + beta - 2.0L);
+                e.w = (double)(alpha - beta - 2.0L);
+                coef[(size_t)(base + (l - l0))] = e;
+                fl[(size_t)(base + (l - l0))] = (double)f_cur;
+                f_prev = f_cur;
+                f_cur = f_next;
+            }
+        }
+    };
+    fill_by_m(total, fill);
+}
+
+// Two-step form of the spin-0 recursion.  With eps_l = sqrt((l^2 - m^2) / (4 l^2 - 1)),
+// h_l = eps_{l+1} eps_{l+2} and c_l = eps_{l+1}^2 + eps_l^2,
+//   h_l lambda_{l+2} = (cos^2 t - c_l) lambda_l - h_{l-2} lambda_{l-2};
+// with lambda_l = f_l mu_l and f_{l+2} f_l h_l constant along a class the last
+// factor becomes 1: t_l = f_l / (h_l f_{l+2}) (cos^2 t - c_l).  The ratio of the
+// first two f of a class is free; it is chosen so that f varies smoothly (the
+// even and the odd steps tend to one limit), which makes t_l -> 2 cos 2t without
+// alternating: only then are t_l - 2 near the poles and t_l + 2 near the equator
+// small, which the difference form needs.  (Relative error of a sum at lmax 2047
+// near the poles, sin t < 0.02: 3.0e-13 with the ratio 1, 3.3e-14 with this one;
+// 3.7e-13 in the one-step form.)
+void build_coef2(const PlanShape &ps, std::vector<Coef4> &coef, std::vector<int64_t> &ofs)
+{
+    ofs.assign(ps.mmax + 1, 0);
+    int64_t total = 0;
+    for (int m = 0; m <= ps.mmax; ++m) {
+        ofs[m] = total - m;
+        total += ps.lmax + 1 - m;
+    }
+    coef.assign((size_t)std::max<int64_t>(total, 1), Coef4{0, 0, 0, 0});
+    auto fill = [&](int first, int step) {
+        std::vector<long double> e, f;
+        for (int m = first; m <= ps.mmax; m += step) {
+            const int n = ps.lmax - m;   // degrees m .. m + n
+            e.resize(n + 5);
+            e[0] = 0.0L;
+            for (int i = 1; i < n + 5; ++i) {
+                const long double l = m + i;
+                e[i] = sqrtl(((long double)i * (2.0L * m + i)) / (4.0L * l * l - 1.0L));
+            }
+            Coef4 *out = &coef[(size_t)(ofs[m] + m)];
+            for (int par = 0; par < 2; ++par) {
+                const int cnt = n >= par ? (n - par) / 2 + 1 : 0;
+                if (!cnt) continue;
+                auto h = [&](int j) { return e[par + 2 * j + 1] * e[par + 2 * j + 2]; };
+                f.assign(cnt + 2, 1.0L);
+                for (int j = 2; j <= cnt; ++j) f[j] = f[j - 2] * h(j - 2) / h(j - 1);
+                f[cnt + 1] = f[cnt - 1] * h(cnt - 1) / h(cnt);
+                long double r = f[cnt] / sqrtl(f[cnt - 1] * f[cnt + 1]);
+                if (cnt & 1) r = 1.0L / r;
+                for (int j = 1; j < cnt + 2; j += 2) f[j] *= r;
+                for (int j = 0; j < cnt; ++j) {
+                    const int i = par + 2 * j;
+                    const long double c = e[i + 1] * e[i + 1] + e[i] * e[i];
+                    const long double al = f[j] / (h(j) * f[j + 1]), be = -al * c;
+                    out[i] = Coef4{(double)al, (double)(al + be - 2.0L), (double)(-(be + 2.0L)), (double)f[j]};
+                }
+            }
+        }
+    };
+    fill_by_m(total, fill);
 }
 
 // Start values lambda_{l0}, l0 = max(m, |s|), from Wigner's formula for the
@@ -581,11 +686,12 @@ int sht_geom_gauss(int nrings, int64_t nphi, double phi0, sht_geom **out)
     if (nrings < 1 || nrings > 65536) { set_error("nrings %d outside [1, 65536]", nrings); return SHT_EINVAL; }
     if (nphi < 1) { set_error("nphi must be >= 1"); return SHT_EINVAL; }
     std::vector<double> th, w;
-    gauss_legendre(nrings, th, w);
+    std::vector<long double> exact;
+    gauss_legendre(nrings, th, w, exact);
     std::vector<int64_t> np(nrings, nphi);
     std::vector<double> p0(nrings, phi0), wt(nrings);
     for (int i = 0; i < nrings; ++i) wt[i] = w[i] * (2.0 * M_PI / (double)nphi);
-    return sht_geom_create(nrings, th.data(), np.data(), p0.data(), wt.data(), nullptr, 1, out);
+    return with_residual(sht_geom_create(nrings, th.data(), np.data(), p0.data(), wt.data(), nullptr, 1, out), exact, out);
 }
 
 int sht_geom_ecp(int nrings, int64_t nphi, int kind, double phi0, sht_geom **out)
@@ -600,11 +706,12 @@ int sht_geom_ecp(int nrings, int64_t nphi, int kind, double phi0, sht_geom **out
     if (nrings < nmin || nrings > 65536) { set_error("nrings %d outside [%d, 65536]", nrings, nmin); return SHT_EINVAL; }
     if (nphi < 1) { set_error("nphi must be >= 1"); return SHT_EINVAL; }
     std::vector<double> th, w;
-    ecp_rule(nrings, kind, th, w);
+    std::vector<long double> exact;
+    ecp_rule(nrings, kind, th, w, exact);
     std::vector<int64_t> np(nrings, nphi);
     std::vector<double> p0(nrings, phi0), wt(nrings);
     for (int i = 0; i < nrings; ++i) wt[i] = w[i] * (2.0 * M_PI / (double)nphi);
-    return sht_geom_create(nrings, th.data(), np.data(), p0.data(), wt.data(), nullptr, 1, out);
+    return with_residual(sht_geom_create(nrings, th.data(), np.data(), p0.data(), wt.data(), nullptr, 1, out), exact, out);
 }
 
 int sht_geom_reduced_gauss(int nrings, int64_t nphi_max, int lmax, int mmax, int spin, double phi0,
@@ -619,7 +726,8 @@ int sht_geom_reduced_gauss(int nrings, int64_t nphi_max, int lmax, int mmax, int
     }
     if (nphi_max < 1) { set_error("nphi_max must be >= 1"); return SHT_EINVAL; }
     std::vector<double> th, w;
-    gauss_legendre(nrings, th, w);
+    std::vector<long double> exact;
+    gauss_legendre(nrings, th, w, exact);
     const double T = std::max(100.0, 0.01 * lmax), sp = (double)spin;
     std::vector<int64_t> np(nrings);
     std::vector<double> p0(nrings, phi0), wt(nrings);
@@ -633,7 +741,7 @@ int sht_geom_reduced_gauss(int nrings, int64_t nphi_max, int lmax, int mmax, int
         np[i] = std::min(n, nphi_max);
         wt[i] = w[i] * (2.0 * M_PI / (double)np[i]);
     }
-    return sht_geom_create(nrings, th.data(), np.data(), p0.data(), wt.data(), nullptr, 1, out);
+    return with_residual(sht_geom_create(nrings, th.data(), np.data(), p0.data(), wt.data(), nullptr, 1, out), exact, out);
 }
 
 int sht_geom_healpix(int nside, sht_geom **out)
@@ -644,8 +752,11 @@ int sht_geom_healpix(int nside, sht_geom **out)
     int nr = 4 * nside - 1;
     std::vector<double> th(nr), p0(nr), wt(nr);
     std::vector<int64_t> np(nr);
+    std::vector<long double> exact(nr);
     for (int i = 1; i <= 2 * nside; ++i) {
         int y = i - 1;
+        exact[y] = i < nside ? 2.0L * asinl(i / (sqrtl(6.0L) * nside)) : acosl((4.0L * nside - 2.0L * i) / (3.0L * nside));
+        exact[nr - 1 - y] = PI_L - exact[y];
         if (i < nside) {
             th[y] = 2.0 * asin(i / (sqrt(6.0) * nside));
             np[y] = 4 * (int64_t)i;
@@ -667,7 +778,7 @@ int sht_geom_healpix(int nside, sht_geom **out)
     th[2 * nside - 1] = 0.5 * M_PI;
     double npix = 12.0 * nside * (double)nside;
     for (int y = 0; y < nr; ++y) wt[y] = 4.0 * M_PI / npix;
-    return sht_geom_create(nr, th.data(), np.data(), p0.data(), wt.data(), nullptr, 1, out);
+    return with_residual(sht_geom_create(nr, th.data(), np.data(), p0.data(), wt.data(), nullptr, 1, out), exact, out);
 }
 
 int sht_geom_info(const sht_geom *g, int *nrings, int64_t *npix)

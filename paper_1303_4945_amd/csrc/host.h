@@ -44,6 +44,7 @@ void mem_stats(int64_t *buffers, int64_t *bytes);
 struct Geom {
     int nrings = 0;
     std::vector<double> theta, phi0, weight;
+    std::vector<double> theta_lo;   // the library's own grids: colatitude = theta + theta_lo (else empty)
     std::vector<int64_t> nphi, ofs;
     int64_t stride = 1;
     bool has_weight = false;
@@ -57,6 +58,7 @@ struct SlotHost {
     int yn = -1, ys = -1;         // ring at t and ring at pi - t (-1: none)
     double cth = 0, sth = 0;      // cos t >= 0, sin t
     double chalf = 0, shalf = 0;  // cos t/2, sin t/2
+    double c2 = 0, s2 = 0;        // cos^2 t, sin^2 t, rounded once
 };
 
 // Per-(m, chain) start value: lambda_{l0} = sign * K * cos(t/2)^p * sin(t/2)^q.
@@ -80,11 +82,16 @@ struct PlanShape {
     double polar_T = 100.0;   // < 0: no polar skipping
 };
 
-void build_slots(const Geom &g, std::vector<SlotHost> &slots);
+// residual: take theta_lo into account
+void build_slots(const Geom &g, std::vector<SlotHost> &slots, bool residual = false);
 // largest m whose terms the polar criterion keeps at this slot (-1: none)
 int slot_mlim(const PlanShape &ps, const SlotHost &s);
 void build_coef(const PlanShape &ps, std::vector<Coef4> &coef, std::vector<double> &fl,
                 std::vector<int64_t> &ofs);
+// spin 0: coefficients of the two-step recursion within one parity class of l + m,
+//   mu_{l+2} = t_l mu_l - mu_{l-2},  t_l = a_l cos^2 t + b_l,  lambda_l = f_l mu_l,
+// as (a_l, a_l + b_l - 2, -(b_l + 2), f_l), laid out as build_coef's tables
+void build_coef2(const PlanShape &ps, std::vector<Coef4> &coef, std::vector<int64_t> &ofs);
 void build_start(const PlanShape &ps, std::vector<StartCoef> &st);
 // (m, slot, l) triples left after polar skipping, slots grouped into tiles
 // whose polar limit is the largest of their slots

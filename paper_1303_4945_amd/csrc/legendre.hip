@@ -37,116 +37,10 @@
 
 #include <type_traits>
 
+#include "legendre_dev.h"
 #include "sht_internal.h"
 
 namespace sht {
-
-typedef double dv4 __attribute__((ext_vector_type(4)));
-typedef float fv4 __attribute__((ext_vector_type(4)));
-
-template <bool F32>
-struct MT;
-template <>
-struct MT<false> {
-    using T = double;
-    using V = dv4;
-};
-template <>
-struct MT<true> {
-    using T = float;
-    using V = fv4;
-};
-
-__device__ __forceinline__ dv4 mfma(double a, double b, dv4 c)
-{
-    return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
-}
-__device__ __forceinline__ fv4 mfma(float a, float b, fv4 c)
-{
-    return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
-}
-
-// Row of the 16x16 result held in register r of this lane (column = lane & 15);
-// the FP64 and FP32 instructions use different result layouts.
-template <bool F32>
-__device__ __forceinline__ int c_row(int lane, int r)
-{
-    return F32 ? 4 * (lane >> 4) + r : (lane >> 4) + 4 * r;
-}
-
-// base^p for base in [0, 1], p >= 0, as mantissa * 2^ex (mantissa in [0.5, 1)).
-__device__ inline void xpow(double base, int p, double &mant, int &ex)
-{
-    mant = 1.0;
-    ex = 0;
-    if (p == 0) return;
-    if (!(base > 0.0)) {
-        mant = 0.0;
-        return;
-    }
-    int eb;
-    double mb = frexp(base, &eb);
-    for (;;) {
-        if (p & 1) {
-            int d;
-            mant = frexp(mant * mb, &d);
-            ex += eb + d;
-        }
-        p >>= 1;
-        if (!p) break;
-        int d;
-        mb = frexp(mb * mb, &d);
-        eb = 2 * eb + d;
-    }
-}
-
-// ---------------------------------------------------------------- recursion
-
-// One recursion chain per lane.  A wavefront runs chains of a single sign
-// (+s or -s), so the per-step coefficients are wave-uniform LDS broadcasts.
-struct Chain {
-    double x;      // cos t
-    double ms2;    // -2 sin^2(t/2)
-    double mu;     // mu_l
-    double aux;    // mu_{l-1} (plain form) or mu_l - mu_{l-1} (difference form)
-    int k;         // scale index (value = mu * 2^(S k)), k <= 0
-};
-
-__device__ inline Chain chain_init(const LegView &v, int m, int slot, int chain)
-{
-    Chain c;
-    c.mu = 0.0;
-    c.aux = 0.0;
-    c.k = 0;
-    c.x = 0.0;
-    c.ms2 = 0.0;
-    if (slot >= v.nslots) return c;
-    const double x = v.slot_cos[slot], st = v.slot_sin[slot];
-    const double sh = v.slot_shalf[slot];
-    c.x = x;
-    c.ms2 = -2.0 * sh * sh;
-    if (v.polar_T >= 0.0) {
-        const double s = (double)v.spin, mm = (double)m;
-        double q = mm * mm + s * s - 2.0 * mm * s * x;
-        double crit = sqrt(q > 0.0 ? q : 0.0) - (double)v.lmax * st;
-        if (crit > v.polar_T) return c;   // skipped term (Sect. 3.3)
-    }
-    const StartCoef sc = v.start[2 * m + chain];
-    double mc, ms;
-    int ec, es;
-    xpow(v.slot_chalf[slot], sc.p, mc, ec);
-    xpow(sh, sc.q, ms, es);
-    int d;
-    double mant = frexp(sc.kmant * mc * ms, &d);
-    if (mant == 0.0) return c;
-    const int e = sc.kexp + ec + es + d;
-    const int S = v.rescale_bits, T = v.thresh_bits;
-    int kk = 0;
-    if (e < T) kk = (T - e) / S;
-    c.k = -kk;
-    c.mu = (double)sc.sign * ldexp(mant, e + S * kk);
-    return c;
-}
 
 // Per-chain step coefficients of one degree, staged in LDS:
 // (alpha_l, +-beta_l, alpha_l +- beta_l - 2, scale * f_l) for the chain's sign;
@@ -245,11 +139,6 @@ __device__ __forceinline__ void chain_chunk_fast(Chain &c, const double4 *__rest
             c.mu = nx;
         }
     }
-}
-
-__device__ __forceinline__ bool wave_any(bool p)
-{
-    return __builtin_amdgcn_ballot_w64(p) != 0;
 }
 
 // wavefronts with a slot of cos t above this use the difference form
@@ -541,6 +430,7 @@ __device__ __forceinline__ void synth_item(const LegView &v, const WaveItem it,
 
     // ring indices of this lane's output rows, all loaded before any store
     int eyn[NSB][4], eys[NSB][4];
+    double escale[SPIN ? 1 : NSB][4];
 #pragma unroll
     for (int sb = 0; sb < NSB; ++sb)
 #pragma unroll
@@ -548,6 +438,7 @@ __device__ __forceinline__ void synth_item(const LegView &v, const WaveItem it,
             const int slot = tile * SPT + sb * 16 + c_row<F32>(lane, r);   // < ntiles * SPT
             eyn[sb][r] = v.slot_yn[slot];
             eys[sb][r] = v.slot_ys[slot];
+            if constexpr (SPIN == 0) escale[sb][r] = v.slot_scale[slot];
         }
 
     // epilogue: ring t = A0 + A1, ring pi - t = sigma (A0 - A1), both times tau_o
@@ -574,7 +465,7 @@ __device__ __forceinline__ void synth_item(const LegView &v, const WaveItem it,
                 const int comp = SPIN ? (o >> 1) : 0, reim = o & 1;
                 const int yn = eyn[sb][r], ys = eys[sb][r];
                 const int64_t rowbase = ((int64_t)t * NCOMP + comp) * v.nrings;
-                const double ts = tneg ? -1.0 : 1.0;   // undo tau_o
+                const double ts = SPIN ? (tneg ? -1.0 : 1.0) : escale[sb][r];   // undo tau_o; slot factor
                 if (yn >= 0) phase[((rowbase + yn) * (v.mmax + 1) + m) * 2 + reim] = ts * (c0 + c1);
                 if (ys >= 0) phase[((rowbase + ys) * (v.mmax + 1) + m) * 2 + reim] = (ssign * ts) * (c0 - c1);
             }
@@ -596,16 +487,6 @@ constexpr int ANA_LC = 32;   // degrees per chunk (16 per parity class)
 // of two 64-slot tiles and 32 columns would not fit the registers
 template <int SPIN, int NCB>
 constexpr int ana_tpw() { return (SPIN == 0 && NCB == 2) ? 1 : 2; }
-
-// Orders the LDS traffic of one wavefront at this point (the LDS executes a
-// wavefront's requests in issue order; this keeps the compiler from moving
-// them across).
-__device__ __forceinline__ void wave_sync()
-{
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
 
 // Work group = one m and a group of transforms.  The m's active slot tiles are
 // taken NW * TPW at a time (TPW per wavefront).  For every chunk of
@@ -776,9 +657,11 @@ __device__ __forceinline__ void anal_item(const LegView &v, const int m, const i
             const bool active = ptile[i] >= 0;
             const int slot0 = active ? ptile[i] * SPT : 0;
             int ynv[KSA], ysv[KSA];
+            double scv[SPIN ? 1 : KSA];
 #pragma unroll
             for (int ks = 0; ks < KSA; ++ks) {
                 const int slot = slot0 + 4 * ks + kk;     // < ntiles * SPT (tables padded)
+                if constexpr (SPIN == 0) scv[ks] = v.slot_scale[slot];
                 const int yn = v.slot_yn[slot], ys = v.slot_ys[slot];
                 const bool ok = active && slot < v.nslots;
                 ynv[ks] = ok ? yn : -1;
@@ -799,7 +682,7 @@ __device__ __forceinline__ void anal_item(const LegView &v, const int m, const i
                     const double gs0 = phase[((rowbase + (ys >= 0 ? ys : 0)) * (v.mmax + 1) + m) * 2 + reim];
                     const double gn = (tok && yn >= 0) ? gn0 : 0.0;
                     const double gs = (tok && ys >= 0) ? ssign * gs0 : 0.0;
-                    const double sg = SPIN ? ((o == 3) ? 1.0 : -1.0) : 1.0;   // -tau_o (spin > 0)
+                    const double sg = SPIN ? ((o == 3) ? 1.0 : -1.0) : scv[SPIN ? 0 : ks];   // -tau_o (spin > 0)
                     gw[i][0][ks][cb] = (T)(sg * (gn + gs));
                     gw[i][1][ks][cb] = (T)(sg * (gn - gs));
                 }
@@ -1154,13 +1037,10 @@ struct SynStage {
 
 // Work item (m, tile group of K tiles from it.tile, J transforms from t0), one wavefront.
 template <int J, int K>
-__global__ __launch_bounds__(64) void k_legendre_synth_valu(LegView v, const WaveItem *__restrict__ items,
-                                                            const double *__restrict__ alm,
-                                                            double *__restrict__ phase)
+__device__ __forceinline__ void synth_valu_item(const LegView &v, const WaveItem it, const double *__restrict__ alm,
+                                                double *__restrict__ phase, SynStage<J> (*st)[VSYN_LC])
 {
     constexpr int LC = VSYN_LC;
-    __shared__ SynStage<J> st[2][LC];
-    const WaveItem it = items[blockIdx.x];
     if (it.m < 0) return;
     const int lane = threadIdx.x;
     const int m = it.m, t0 = it.t0, lmax = v.lmax;
@@ -1250,16 +1130,26 @@ __global__ __launch_bounds__(64) void k_legendre_synth_valu(LegView v, const Wav
         const int slot = tile[k] * 64 + lane;
         if (slot >= v.nslots) continue;
         const int yn = v.slot_yn[slot], ys = v.slot_ys[slot];
+        const double sc = v.slot_scale[slot];
 #pragma unroll
         for (int tr = 0; tr < J; ++tr) {
             const int t = t0 + tr;
             if (t >= v.ntrans) break;
             const int64_t rowbase = (int64_t)t * v.nrings;
             const double2 a0 = acc[0][k][tr], a1 = acc[1][k][tr];
-            if (yn >= 0) ph[(rowbase + yn) * (v.mmax + 1) + m] = make_double2(a0.x + a1.x, a0.y + a1.y);
-            if (ys >= 0) ph[(rowbase + ys) * (v.mmax + 1) + m] = make_double2(a0.x - a1.x, a0.y - a1.y);
+            if (yn >= 0) ph[(rowbase + yn) * (v.mmax + 1) + m] = make_double2(sc * (a0.x + a1.x), sc * (a0.y + a1.y));
+            if (ys >= 0) ph[(rowbase + ys) * (v.mmax + 1) + m] = make_double2(sc * (a0.x - a1.x), sc * (a0.y - a1.y));
         }
     }
+}
+
+template <int J, int K>
+__global__ __launch_bounds__(64) void k_legendre_synth_valu(LegView v, const WaveItem *__restrict__ items,
+                                                            const double *__restrict__ alm,
+                                                            double *__restrict__ phase)
+{
+    __shared__ SynStage<J> st[2][VSYN_LC];
+    synth_valu_item<J, K>(v, items[blockIdx.x], alm, phase, st);
 }
 
 // staged data of one degree of the spin vector synthesis
@@ -1280,13 +1170,10 @@ struct SynStageS {
 // (spin-1 plan): one input component per transform, E = sqrt(l (l + 1)) a_lm
 // and B = 0.
 template <int J, int K>
-__global__ __launch_bounds__(64) void k_legendre_synth_valu_s(LegView v, const WaveItem *__restrict__ items,
-                                                              const double *__restrict__ alm,
-                                                              double *__restrict__ phase, int deriv)
+__device__ __forceinline__ void synth_valu_s_item(const LegView &v, const WaveItem it, const double *__restrict__ alm,
+                                                  double *__restrict__ phase, int deriv, SynStageS<J> (*st)[VSYN_LC])
 {
     constexpr int LC = VSYN_LC;
-    __shared__ SynStageS<J> st[2][LC];
-    const WaveItem it = items[blockIdx.x];
     if (it.m < 0) return;
     const int lane = threadIdx.x;
     const int m = it.m, t0 = it.t0, lmax = v.lmax;
@@ -1420,6 +1307,35 @@ __global__ __launch_bounds__(64) void k_legendre_synth_valu_s(LegView v, const W
     }
 }
 
+template <int J, int K>
+__global__ __launch_bounds__(64) void k_legendre_synth_valu_s(LegView v, const WaveItem *__restrict__ items,
+                                                              const double *__restrict__ alm,
+                                                              double *__restrict__ phase, int deriv)
+{
+    __shared__ SynStageS<J> st[2][VSYN_LC];
+    synth_valu_s_item<J, K>(v, items[blockIdx.x], alm, phase, deriv, st);
+}
+
+// A spin-1 or spin-2 plan with a scalar part in one launch: the first nown work
+// items are the plan's own (slots near the poles, spin chains), the others the
+// scalar part's (K slots per lane).  Both are chains of lmax serial steps that a
+// small plan is too short to hide one after the other: N_side 128, lmax 383, one
+// spin-2 transform 42 + 30 us as two launches.
+template <int K>
+__global__ __launch_bounds__(64) void k_legendre_synth_valu_split(LegView v, const WaveItem *__restrict__ items,
+                                                                  const double *__restrict__ alm, int nown, LegView vq,
+                                                                  const WaveItem *__restrict__ items_q,
+                                                                  const double *__restrict__ alm_q,
+                                                                  double *__restrict__ phase, int deriv)
+{
+    __shared__ union {
+        SynStage<2> q[2][VSYN_LC];
+        SynStageS<1> s[2][VSYN_LC];
+    } st;
+    if ((int)blockIdx.x < nown) synth_valu_s_item<1, 1>(v, items[blockIdx.x], alm, phase, deriv, st.s);
+    else synth_valu_item<2, K>(vq, items_q[blockIdx.x - nown], alm_q, phase, st.q);
+}
+
 // ---- butterfly reduction of 32 values over the 64 lanes of a wavefront
 
 __device__ __forceinline__ double dpp_f64(double x, int ctrl)
@@ -1501,22 +1417,27 @@ constexpr int ANV_CH = 64;  // degrees x transforms per chunk of the vector anal
 // Work group = one m and J transforms from blockIdx.y J; the m's active tiles
 // are dealt K per wavefront, NW K per pass, and every pass after the first
 // adds into the m's a_lm row.
-template <int J, int K>
-__global__ __launch_bounds__(64 * ANV_NW) void k_legendre_anal_valu(LegView v, const int *__restrict__ mlist,
-                                                                   const double *__restrict__ phase,
-                                                                   double *__restrict__ alm, int mode)
+template <int J, int NWM>
+struct AnvShared {
+    static constexpr int LC = ANV_CH / J, NV = LC * J * 2;
+    // per wavefront, value and octet lane: the octet's 8 partial sums of the value
+    double part[2][NWM][NV * 8];
+    double4 stq[2][LC];
+};
+
+// NWM: wavefronts per work group at most
+template <int J, int K, int NWM>
+__device__ __forceinline__ void anal_valu_item(const LegView &v, const int m, const int t0,
+                                               const double *__restrict__ phase, double *__restrict__ alm, int mode,
+                                               AnvShared<J, NWM> &sh)
 {
     constexpr int LC = ANV_CH / J;       // degrees per chunk (one barrier and output round each)
     constexpr int NV = LC * J * 2;       // output values of a chunk
     constexpr int GD = 4 / J;            // degrees per reduction group: 8 values
     static_assert(GD * J * 2 == 8 && LC % GD == 0 && LC <= 64, "value layout");
     constexpr int OPT = (NV + 63) / 64;  // output values per thread (at least one wavefront)
-    constexpr int NWM = J == 1 ? 2 : ANV_NW;   // wavefronts per work group at most (launcher)
-    // per wavefront, value and octet lane: the octet's 8 partial sums of the value
-    __shared__ double part[2][NWM][NV * 8];
-    __shared__ double4 stq[2][LC];
-    const int m = mlist[blockIdx.x];
-    const int t0 = (int)blockIdx.y * J;
+    auto &part = sh.part;
+    auto &stq = sh.stq;
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
     const int nw = (int)(blockDim.x >> 6);
     const int lmax = v.lmax, l0 = m;
@@ -1567,6 +1488,7 @@ __global__ __launch_bounds__(64 * ANV_NW) void k_legendre_anal_valu(LegView v, c
             const int slot = tile[k] >= 0 ? tile[k] * 64 + lane : v.nslots;
             const bool ok = slot < v.nslots;
             const int yn = ok ? v.slot_yn[slot] : -1, ys = ok ? v.slot_ys[slot] : -1;
+            const double sc = ok ? v.slot_scale[slot] : 0.0;
 #pragma unroll
             for (int tr = 0; tr < J; ++tr) {
                 const bool tok = t0 + tr < v.ntrans;
@@ -1575,8 +1497,8 @@ __global__ __launch_bounds__(64 * ANV_NW) void k_legendre_anal_valu(LegView v, c
                 const double2 gs0 = G[(rowbase + (ys >= 0 ? ys : 0)) * (v.mmax + 1) + m];
                 const double2 gn = (tok && yn >= 0) ? gn0 : make_double2(0.0, 0.0);
                 const double2 gs = (tok && ys >= 0) ? gs0 : make_double2(0.0, 0.0);
-                g[k][0][tr] = make_double2(gn.x + gs.x, gn.y + gs.y);
-                g[k][1][tr] = make_double2(gn.x - gs.x, gn.y - gs.y);
+                g[k][0][tr] = make_double2(sc * (gn.x + gs.x), sc * (gn.y + gs.y));
+                g[k][1][tr] = make_double2(sc * (gn.x - gs.x), sc * (gn.y - gs.y));
             }
         }
         // staged step coefficients (alpha, beta, alpha + beta - 2, f_l) of a
@@ -1667,6 +1589,18 @@ __global__ __launch_bounds__(64 * ANV_NW) void k_legendre_anal_valu(LegView v, c
     }
 }
 
+template <int J>
+constexpr int anv_nwm() { return J == 1 ? 2 : ANV_NW; }   // (launcher)
+
+template <int J, int K>
+__global__ __launch_bounds__(64 * ANV_NW) void k_legendre_anal_valu(LegView v, const int *__restrict__ mlist,
+                                                                   const double *__restrict__ phase,
+                                                                   double *__restrict__ alm, int mode)
+{
+    __shared__ AnvShared<J, anv_nwm<J>()> sh;
+    anal_valu_item<J, K, anv_nwm<J>()>(v, mlist[blockIdx.x], (int)blockIdx.y * J, phase, alm, mode, sh);
+}
+
 // Spin s > 0 analysis (transposed column maps of the spin synthesis): per
 // degree and slot W = -(mu_+ + mu_-), X = mu_+ - mu_-, and per transform
 //   E_re += W GW_Qre + X GX_Uim,   E_im += W GW_Qim - X GX_Ure,
@@ -1677,22 +1611,27 @@ __global__ __launch_bounds__(64 * ANV_NW) void k_legendre_anal_valu(LegView v, c
 // the spin-0 kernel (4 values per degree and transform), the slots dealt in
 // units of 64 (two 32-slot tiles).  Adjoint of the derivative synthesis: E
 // alone, times sqrt(l (l + 1)), one output component per transform.
-template <int J, int K>
-__global__ __launch_bounds__(64 * ANV_NW) void k_legendre_anal_valu_s(LegView v, const int *__restrict__ mlist,
-                                                                     const double *__restrict__ phase,
-                                                                     double *__restrict__ alm, int mode)
+template <int J, int NWM>
+struct AnvSharedS {
+    static constexpr int LC = ANV_CH / (2 * J), NV = LC * J * 4;
+    double part[2][NWM][NV * 8];   // octet partial sums per value
+    double4 stq[2][LC];
+    double stf[2][LC];
+};
+
+template <int J, int K, int NWM>
+__device__ __forceinline__ void anal_valu_s_item(const LegView &v, const int m, const int t0,
+                                                 const double *__restrict__ phase, double *__restrict__ alm, int mode,
+                                                 AnvSharedS<J, NWM> &sh)
 {
     constexpr int LC = ANV_CH / (2 * J);   // degrees per chunk
     constexpr int NV = LC * J * 4;         // output values of a chunk: (E, B) x (re, im) per transform
     constexpr int GD = 2;                  // degrees per reduction group: 8 values (one transform)
     static_assert(J == 1 && LC % GD == 0 && LC <= 64, "value layout");
     constexpr int OPT = (NV + 63) / 64;
-    constexpr int NWM = 2;   // wavefronts per work group at most (launcher)
-    __shared__ double part[2][NWM][NV * 8];   // octet partial sums per value
-    __shared__ double4 stq[2][LC];
-    __shared__ double stf[2][LC];
-    const int m = mlist[blockIdx.x];
-    const int t0 = (int)blockIdx.y * J;
+    auto &part = sh.part;
+    auto &stq = sh.stq;
+    auto &stf = sh.stf;
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
     const int nw = (int)(blockDim.x >> 6);
     const int lmax = v.lmax;
@@ -1757,7 +1696,8 @@ __global__ __launch_bounds__(64 * ANV_NW) void k_legendre_anal_valu_s(LegView v,
 #pragma unroll
         for (int k = 0; k < K; ++k) {
             const int slot = tile[k] >= 0 ? tile[k] * 64 + lane : v.nslots;
-            const bool ok = slot < v.nslots;
+            // (a 32-slot tile that the polar criterion drops at this m has no phases)
+            const bool ok = slot < v.nslots && v.tile_mlim[slot >> 5] >= m;
             const int yn = ok ? v.slot_yn[slot] : -1, ys = ok ? v.slot_ys[slot] : -1;
 #pragma unroll
             for (int tr = 0; tr < J; ++tr) {
@@ -1866,6 +1806,33 @@ __global__ __launch_bounds__(64 * ANV_NW) void k_legendre_anal_valu_s(LegView v,
     }
 }
 
+template <int J, int K>
+__global__ __launch_bounds__(64 * ANV_NW) void k_legendre_anal_valu_s(LegView v, const int *__restrict__ mlist,
+                                                                     const double *__restrict__ phase,
+                                                                     double *__restrict__ alm, int mode)
+{
+    __shared__ AnvSharedS<J, 2> sh;
+    anal_valu_s_item<J, K, 2>(v, mlist[blockIdx.x], (int)blockIdx.y * J, phase, alm, mode, sh);
+}
+
+// Plan with a scalar part: work groups of both in one launch, as in the synthesis
+// (per transform t = blockIdx.y, the first nown groups are the plan's own).
+template <int K>
+__global__ __launch_bounds__(64 * ANV_NW) void k_legendre_anal_valu_split(LegView v, const int *__restrict__ mlist,
+                                                                         int nown, double *__restrict__ alm, int mode,
+                                                                         LegView vq, const int *__restrict__ mlist_q,
+                                                                         double *__restrict__ alm_q,
+                                                                         const double *__restrict__ phase)
+{
+    __shared__ union {
+        AnvShared<2, ANV_NW> q;
+        AnvSharedS<1, ANV_NW> s;
+    } sh;
+    const int t = (int)blockIdx.y;
+    if ((int)blockIdx.x < nown) anal_valu_s_item<1, 1, ANV_NW>(v, mlist[blockIdx.x], t, phase, alm, mode, sh.s);
+    else anal_valu_item<2, K, ANV_NW>(vq, mlist_q[blockIdx.x - nown], 2 * t, phase, alm_q, 0, sh.q);
+}
+
 __global__ void k_reset_counter(unsigned *counter)
 
 {
@@ -1892,12 +1859,12 @@ int anal_ncb(int spin, int ntrans)
 int anal_tpw_built(int spin, int ncb) { return spin ? ana_tpw<2, 1>() : (ncb == 2 ? ana_tpw<0, 2>() : ana_tpw<0, 1>()); }
 
 // default column blocks per synthesis wavefront (the autotuner may change it)
-int synth_ncb_default(int spin, int ntrans, int precision)
+int synth_ncb_default(const Plan &p)
 {
-    (void)precision;
-    if (spin == 0) return 1;      // 64-slot tiles: two column blocks would need 1 wavefront/SIMD
-    const int cols = ntrans * 4;
-    return cols > 16 ? 2 : 1;
+    if (two_step(p)) return synth0_ncb(p);
+    // FP32 spin 0: two column blocks of 64-slot tiles would need one wavefront per SIMD
+    if (p.spin == 0) return 1;
+    return p.ntrans * 4 > 16 ? 2 : 1;
 }
 
 template <int SPIN, int NCB, bool F32>
@@ -1913,7 +1880,7 @@ static void launch_anal_t(const Plan &p, const LegView &v, const double *phase, 
                           int mode, hipStream_t s)
 {
     const int jpg = NCB * 16 / (SPIN ? 4 : 2);
-    dim3 grid((unsigned)(p.mmax + 1), (unsigned)((p.ntrans + jpg - 1) / jpg));
+    dim3 grid((unsigned)p.anal_ms.size(), (unsigned)((p.ntrans + jpg - 1) / jpg));
     hipLaunchKernelGGL((k_legendre_anal<SPIN, NCB, F32>), grid, dim3(64 * ana_nw(F32, SPIN != 0)), 0, s, v,
                        p.d_anal_ms, phase, alm, jpg, mode);
 }
@@ -1924,7 +1891,8 @@ static int dispatch_synth(const Plan &p, const LegView &v, const double *alm, do
 {
     const int ncb = p.tune.synth_ncb;
     if (p.spin == 0) {
-        if (ncb == 1) launch_synth_t<0, 1, F32>(p, v, alm, phase, 0, s);
+        if constexpr (!F32) return launch_legendre_synth0(p, alm, phase, s);
+        else if (ncb == 1) launch_synth_t<0, 1, F32>(p, v, alm, phase, 0, s);
         else if (ncb == 2) launch_synth_t<0, 2, F32>(p, v, alm, phase, 0, s);
         else return SHT_EINVAL;
     } else {
@@ -1941,7 +1909,8 @@ static void dispatch_anal(const Plan &p, const LegView &v, const double *phase, 
 {
     const int ncb = p.tune.anal_ncb;
     if (p.spin == 0) {
-        if (ncb == 1) launch_anal_t<0, 1, F32>(p, v, phase, alm, mode, s);
+        if constexpr (!F32) (void)launch_legendre_anal0(p, phase, alm, mode, s);   // its error is read below
+        else if (ncb == 1) launch_anal_t<0, 1, F32>(p, v, phase, alm, mode, s);
         else launch_anal_t<0, 2, F32>(p, v, phase, alm, mode, s);
     } else {
         if (ncb == 1) launch_anal_t<2, 1, F32>(p, v, phase, alm, mode, s);
@@ -1961,10 +1930,17 @@ int valu_k(const Plan &p, bool anal)
 {
     // analysis, spin 0: four slots per lane (registers 208 for one transform,
     // 239 for two; six would leave one wavefront per SIMD); otherwise two
-    const int kmax = (anal && p.spin == 0) ? 4 : 2;
+    // (the few slots that a scalar part leaves to its plan: one)
+    const int kmax = p.eq ? 1 : (anal && p.spin == 0) ? 4 : 2;
     const int units = (p.nslots + 63) / 64;   // 64-slot units (spin plans: two tiles each)
     const int k = units >= 8 ? 4 : (units >= 2 ? 2 : 1);
     return k < kmax ? k : kmax;
+}
+
+int synth_tile_step(const Plan &p)
+{
+    if (p.tune.valu) return valu_k(p, false) * (64 / p.slots_per_tile);
+    return two_step(p) ? 2 : 1;   // work groups of up to four 32-slot wavefronts
 }
 
 template <int J, int K>
@@ -1984,7 +1960,7 @@ static void launch_anal_valu_t(const Plan &p, const LegView &v, const double *ph
     const int groups = (p.ntiles + K - 1) / K;
     const int nwmax = J == 1 ? 2 : ANV_NW;
     const int nw = groups < nwmax ? (groups > 0 ? groups : 1) : nwmax;
-    const dim3 grid((unsigned)(p.mmax + 1), (unsigned)((p.ntrans + J - 1) / J));
+    const dim3 grid((unsigned)p.anal_ms.size(), (unsigned)((p.ntrans + J - 1) / J));
     hipLaunchKernelGGL((k_legendre_anal_valu<J, K>), grid, dim3(64 * nw), 0, s, v, p.d_anal_ms, phase, alm, mode);
 }
 
@@ -2002,7 +1978,7 @@ static void launch_anal_valu_s_t(const Plan &p, const LegView &v, const double *
 {
     const int groups = ((p.nslots + 63) / 64 + K - 1) / K;
     const int nw = groups < 2 ? (groups > 0 ? groups : 1) : 2;
-    const dim3 grid((unsigned)(p.mmax + 1), (unsigned)p.ntrans);
+    const dim3 grid((unsigned)p.anal_ms.size(), (unsigned)p.ntrans);
     hipLaunchKernelGGL((k_legendre_anal_valu_s<1, K>), grid, dim3(64 * nw), 0, s, v, p.d_anal_ms, phase, alm, mode);
 }
 
@@ -2025,8 +2001,42 @@ static void anal_valu_k(const Plan &p, const LegView &v, const double *phase, do
     }
 }
 
+// Vector kernels of a plan with a scalar part (which then holds pairs of transforms).
+template <int K>
+static void launch_synth_valu_split_t(const Plan &p, const double *alm, double *phase, int deriv, hipStream_t s)
+{
+    const int nown = (int)p.synth_items.size();
+    hipLaunchKernelGGL(k_legendre_synth_valu_split<K>, dim3((unsigned)(nown + p.eq->synth_items.size())), dim3(64), 0, s,
+                       make_leg_view(p), p.d_synth_items, alm, nown, make_leg_view(*p.eq), p.eq->d_synth_items,
+                       p.d_band_alm, phase, deriv);
+}
+
+template <int K>
+static void launch_anal_valu_split_t(const Plan &p, const double *phase, double *alm, int mode, hipStream_t s)
+{
+    const Plan &e = *p.eq;
+    const int nown = (int)p.anal_ms.size();
+    const int groups = (e.ntiles + K - 1) / K;
+    const int nw = groups < ANV_NW ? (groups > 0 ? groups : 1) : ANV_NW;
+    const dim3 grid((unsigned)(nown + e.anal_ms.size()), (unsigned)p.ntrans);
+    hipLaunchKernelGGL(k_legendre_anal_valu_split<K>, grid, dim3(64 * nw), 0, s, make_leg_view(p), p.d_anal_ms, nown,
+                       alm, mode, make_leg_view(e), e.d_anal_ms, p.d_band_alm, phase);
+}
+
 int launch_legendre_synth(const Plan &p, const double *alm, double *phase, bool deriv, hipStream_t s)
 {
+    if (p.eq) {   // scalar part: banded coefficients, then its own spin-0 launch
+        int rc = launch_band_synth(p, alm, p.d_band_alm, deriv, s);
+        if (rc) return rc;
+        if (p.tune.valu) {
+            log_msg(3, "launch Legendre synthesis plan %llu: %zu + %zu items, vector-unit kernels, stream %p",
+                    (unsigned long long)p.serial, p.synth_items.size(), p.eq->synth_items.size(), (void *)s);
+            if (valu_k(*p.eq, false) == 2) launch_synth_valu_split_t<2>(p, alm, phase, deriv ? 1 : 0, s);
+            else launch_synth_valu_split_t<1>(p, alm, phase, deriv ? 1 : 0, s);
+            return check_hip(hipGetLastError(), "legendre synthesis launch");
+        }
+        if ((rc = launch_legendre_synth(*p.eq, p.d_band_alm, phase, false, s))) return rc;
+    }
     if (p.synth_items.empty()) return SHT_OK;
     const LegView v = make_leg_view(p);
     log_msg(3, "launch Legendre synthesis plan %llu: %zu items, %s kernels%s, stream %p",
@@ -2052,11 +2062,12 @@ int launch_legendre_synth(const Plan &p, const double *alm, double *phase, bool 
     return check_hip(hipGetLastError(), "legendre synthesis launch");
 }
 
-int launch_legendre_anal(const Plan &p, const double *phase, double *alm, int mode, hipStream_t s)
+static int launch_legendre_anal_own(const Plan &p, const double *phase, double *alm, int mode, hipStream_t s)
 {
+    if (p.anal_ms.empty()) return SHT_OK;
     const LegView v = make_leg_view(p);
     log_msg(3, "launch Legendre analysis plan %llu: %d m values x %d transforms, %s kernels, mode %d, stream %p",
-            (unsigned long long)p.serial, p.mmax + 1, p.ntrans, p.tune.valu ? "vector-unit" : "matrix-core", mode,
+            (unsigned long long)p.serial, (int)p.anal_ms.size(), p.ntrans, p.tune.valu ? "vector-unit" : "matrix-core", mode,
             (void *)s);
     if (p.tune.valu && p.spin == 0) {
         if (valu_jpg(p) == 1) anal_valu_k<1>(p, v, phase, alm, mode, s);
@@ -2073,22 +2084,28 @@ int launch_legendre_anal(const Plan &p, const double *phase, double *alm, int mo
     return check_hip(hipGetLastError(), "legendre analysis launch");
 }
 
-// ---------------------------------------------------------------- batches
-
-// work groups of a persistent launch on a device: every CU filled to the
-// kernel's occupancy
-template <typename K>
-static int persistent_groups(K kernel, int threads, int dev)
+int launch_legendre_anal(const Plan &p, const double *phase, double *alm, int mode, hipStream_t s)
 {
-    int ncu = 0, per_cu = 0;
-    if (hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
-        hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, (const void *)kernel, threads, 0) != hipSuccess) {
-        (void)hipGetLastError();
-        return 1024;
+    int rc;
+    if (p.eq && p.tune.valu) {
+        log_msg(3, "launch Legendre analysis plan %llu: %zu + %zu m values x %d transforms, vector-unit kernels, stream %p",
+                (unsigned long long)p.serial, p.anal_ms.size(), p.eq->anal_ms.size(), p.ntrans, (void *)s);
+        switch (valu_k(*p.eq, true)) {
+        case 4: launch_anal_valu_split_t<4>(p, phase, alm, mode, s); break;
+        case 2: launch_anal_valu_split_t<2>(p, phase, alm, mode, s); break;
+        default: launch_anal_valu_split_t<1>(p, phase, alm, mode, s); break;
+        }
+        if ((rc = check_hip(hipGetLastError(), "legendre analysis launch"))) return rc;
+        return launch_band_anal(p, p.d_band_alm, alm, mode, s);
     }
-    const int g = ncu * (per_cu > 0 ? per_cu : 1);
-    return g > 0 ? g : 1024;
+    rc = launch_legendre_anal_own(p, phase, alm, mode, s);
+    if (rc || !p.eq) return rc;
+    // scalar part: its sums, then the transposed band, added to the plan's own
+    if ((rc = launch_legendre_anal_own(*p.eq, phase, p.d_band_alm, 0, s))) return rc;
+    return launch_band_anal(p, p.d_band_alm, alm, mode, s);
 }
+
+// ---------------------------------------------------------------- batches
 
 template <int SPIN, int NCB, bool F32>
 static int anal_batch_groups_t(int dev)
@@ -2100,9 +2117,8 @@ int anal_batch_groups(int spin, int ncb, bool f32, int dev)
 {
     const int key = (spin ? 4 : 0) + (ncb == 2 ? 2 : 0) + (f32 ? 1 : 0);
     switch (key) {
-    case 0: return anal_batch_groups_t<0, 1, false>(dev);
+    case 0: case 2: return anal0_batch_groups(ncb, dev);
     case 1: return anal_batch_groups_t<0, 1, true>(dev);
-    case 2: return anal_batch_groups_t<0, 2, false>(dev);
     case 3: return anal_batch_groups_t<0, 2, true>(dev);
     case 4: return anal_batch_groups_t<2, 1, false>(dev);
     case 5: return anal_batch_groups_t<2, 1, true>(dev);
@@ -2121,9 +2137,8 @@ int synth_batch_groups(int spin, int ncb, bool f32, int dev)
 {
     const int key = (spin ? 4 : 0) + (ncb == 2 ? 2 : 0) + (f32 ? 1 : 0);
     switch (key) {
-    case 0: return synth_batch_groups_t<0, 1, false>(dev);
+    case 0: case 2: return synth0_batch_groups(ncb, dev);
     case 1: return synth_batch_groups_t<0, 1, true>(dev);
-    case 2: return synth_batch_groups_t<0, 2, false>(dev);
     case 3: return synth_batch_groups_t<0, 2, true>(dev);
     case 4: return synth_batch_groups_t<2, 1, false>(dev);
     case 5: return synth_batch_groups_t<2, 1, true>(dev);
@@ -2139,8 +2154,11 @@ static void launch_synth_batch_t(const Batch &b, const BatchPtrs &ptrs, int deri
     SynQueues q;
     for (int d = 0; d <= NUM_XCD; ++d) q.ofs[d] = b.syn_ofs[d];
     hipLaunchKernelGGL(k_reset_counters, dim3(1), dim3(64), 0, s, counters, NUM_XCD, 16);
-    hipLaunchKernelGGL((k_legendre_synth_batch<SPIN, NCB, F32>), dim3((unsigned)b.syn_groups), dim3(64), 0, s,
-                       b.d_views, b.d_syn, q, ptrs, b.syn_flush, deriv, counters);
+    if constexpr (SPIN == 0 && !F32)
+        launch_synth0_batch(b, ptrs, q, counters, s);
+    else
+        hipLaunchKernelGGL((k_legendre_synth_batch<SPIN, NCB, F32>), dim3((unsigned)b.syn_groups), dim3(64), 0, s,
+                           b.d_views, b.d_syn, q, ptrs, b.syn_flush, deriv, counters);
 }
 
 int launch_legendre_synth_batch(const Batch &b, const BatchPtrs &ptrs, bool deriv, hipStream_t s)
@@ -2167,9 +2185,11 @@ int launch_legendre_synth_batch(const Batch &b, const BatchPtrs &ptrs, bool deri
 template <int SPIN, int NCB, bool F32>
 static void launch_anal_batch_t(const Batch &b, const BatchPtrs &ptrs, int mode, hipStream_t s)
 {
-    auto k = k_legendre_anal_batch<SPIN, NCB, F32>;
     hipLaunchKernelGGL(k_reset_counter, dim3(1), dim3(64), 0, s, b.d_counter);
-    hipLaunchKernelGGL(k, dim3((unsigned)b.ana_groups), dim3(64 * ana_nw(F32, SPIN != 0)), 0, s, b.d_views, b.d_ana,
+    if constexpr (SPIN == 0 && !F32)
+        launch_anal0_batch(b, ptrs, mode, s);
+    else
+        hipLaunchKernelGGL((k_legendre_anal_batch<SPIN, NCB, F32>), dim3((unsigned)b.ana_groups), dim3(64 * ana_nw(F32, SPIN != 0)), 0, s, b.d_views, b.d_ana,
                        b.nana, ptrs, mode, b.d_counter);
 }
 

@@ -1,0 +1,147 @@
+// Device helpers shared by the Legendre kernels (legendre.hip, legendre0.hip).
+#pragma once
+
+#include <hip/hip_runtime.h>
+
+#include "sht_internal.h"
+
+namespace sht {
+
+typedef double dv4 __attribute__((ext_vector_type(4)));
+typedef float fv4 __attribute__((ext_vector_type(4)));
+
+template <bool F32>
+struct MT;
+template <>
+struct MT<false> {
+    using T = double;
+    using V = dv4;
+};
+template <>
+struct MT<true> {
+    using T = float;
+    using V = fv4;
+};
+
+__device__ __forceinline__ dv4 mfma(double a, double b, dv4 c)
+{
+    return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
+}
+__device__ __forceinline__ fv4 mfma(float a, float b, fv4 c)
+{
+    return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
+}
+
+// Row of the 16x16 result held in register r of this lane (column = lane & 15);
+// the FP64 and FP32 instructions use different result layouts.
+template <bool F32>
+__device__ __forceinline__ int c_row(int lane, int r)
+{
+    return F32 ? 4 * (lane >> 4) + r : (lane >> 4) + 4 * r;
+}
+
+// base^p for base in [0, 1], p >= 0, as mantissa * 2^ex (mantissa in [0.5, 1)).
+__device__ inline void xpow(double base, int p, double &mant, int &ex)
+{
+    mant = 1.0;
+    ex = 0;
+    if (p == 0) return;
+    if (!(base > 0.0)) {
+        mant = 0.0;
+        return;
+    }
+    int eb;
+    double mb = frexp(base, &eb);
+    for (;;) {
+        if (p & 1) {
+            int d;
+            mant = frexp(mant * mb, &d);
+            ex += eb + d;
+        }
+        p >>= 1;
+        if (!p) break;
+        int d;
+        mb = frexp(mb * mb, &d);
+        eb = 2 * eb + d;
+    }
+}
+
+// ---------------------------------------------------------------- recursion
+
+// One recursion chain per lane.  A wavefront runs chains of a single sign
+// (+s or -s), so the per-step coefficients are wave-uniform LDS broadcasts.
+struct Chain {
+    double x;      // cos t
+    double ms2;    // -2 sin^2(t/2)
+    double mu;     // mu_l
+    double aux;    // mu_{l-1} (plain form) or mu_l - mu_{l-1} (difference form)
+    int k;         // scale index (value = mu * 2^(S k)), k <= 0
+};
+
+__device__ inline Chain chain_init(const LegView &v, int m, int slot, int chain)
+{
+    Chain c;
+    c.mu = 0.0;
+    c.aux = 0.0;
+    c.k = 0;
+    c.x = 0.0;
+    c.ms2 = 0.0;
+    if (slot >= v.nslots) return c;
+    const double x = v.slot_cos[slot], st = v.slot_sin[slot];
+    const double sh = v.slot_shalf[slot];
+    c.x = x;
+    c.ms2 = -2.0 * sh * sh;
+    if (v.polar_T >= 0.0) {
+        const double s = v.crit_spin, mm = (double)m;
+        double q = mm * mm + s * s - 2.0 * mm * s * x;
+        double crit = sqrt(q > 0.0 ? q : 0.0) - v.crit_lmax * st;
+        if (crit > v.polar_T) return c;   // skipped term (Sect. 3.3)
+    }
+    const StartCoef sc = v.start[2 * m + chain];
+    double mc, ms;
+    int ec, es;
+    xpow(v.slot_chalf[slot], sc.p, mc, ec);
+    xpow(sh, sc.q, ms, es);
+    int d;
+    double mant = frexp(sc.kmant * mc * ms, &d);
+    if (mant == 0.0) return c;
+    const int e = sc.kexp + ec + es + d;
+    const int S = v.rescale_bits, T = v.thresh_bits;
+    int kk = 0;
+    if (e < T) kk = (T - e) / S;
+    c.k = -kk;
+    c.mu = (double)sc.sign * ldexp(mant, e + S * kk);
+    return c;
+}
+
+__device__ __forceinline__ bool wave_any(bool p)
+{
+    return __builtin_amdgcn_ballot_w64(p) != 0;
+}
+
+// Orders the LDS traffic of one wavefront at this point (the LDS executes a
+// wavefront's requests in issue order; this keeps the compiler from moving
+// them across).
+__device__ __forceinline__ void wave_sync()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// work groups of a persistent launch on a device: every CU filled to the
+// kernel's occupancy
+template <typename K>
+inline int persistent_groups(K kernel, int threads, int dev)
+{
+    int ncu = 0, per_cu = 0;
+    if (hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
+        hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, (const void *)kernel, threads, 0) != hipSuccess) {
+        (void)hipGetLastError();
+        return 1024;
+    }
+    const int g = ncu * (per_cu > 0 ? per_cu : 1);
+    return g > 0 ? g : 1024;
+}
+
+}  // namespace sht

@@ -1448,14 +1448,14 @@ int fft_plan_build(Plan &p)
     }
     // per-ring tables
     std::vector<int> slot_of_ring(g.nrings, -1);
-    for (int i = 0; i < p.nslots; ++i) {
+    for (int i = 0; i < (int)p.slots.size(); ++i) {
         if (p.slots[i].yn >= 0) slot_of_ring[p.slots[i].yn] = i;
         if (p.slots[i].ys >= 0) slot_of_ring[p.slots[i].ys] = i;
     }
     std::vector<int> mvalid(g.nrings, -1);
     for (int y = 0; y < g.nrings; ++y) {
         int sl = slot_of_ring[y];
-        mvalid[y] = (sl >= 0) ? p.tile_mlim[sl / p.slots_per_tile] : -1;
+        mvalid[y] = (sl >= 0) ? slot_phase_mlim(p, sl) : -1;
     }
     const int ncoarse = p.mmax / 64 + 1;
     const int nrot = 64 + ncoarse;

@@ -83,21 +83,25 @@ static void plan_free_device(Plan *p)
     dev_free(p->d_slot_cos); dev_free(p->d_slot_sin);
     dev_free(p->d_slot_chalf); dev_free(p->d_slot_shalf);
     dev_free(p->d_slot_yn); dev_free(p->d_slot_ys);
-    dev_free(p->d_coef); dev_free(p->d_fl); dev_free(p->d_coef_ofs); dev_free(p->d_start);
+    dev_free(p->d_coef); dev_free(p->d_coef2); dev_free(p->d_fl); dev_free(p->d_coef_ofs); dev_free(p->d_start);
     dev_free(p->d_tile_mlim); dev_free(p->d_synth_items); dev_free(p->d_anal_ms);
     dev_free(p->d_zeros);
     dev_free(p->d_dfac);
     dev_free(p->d_rh);
     dev_free(p->d_phase);
+    dev_free(p->d_slot_scale); dev_free(p->d_band); dev_free(p->d_band_alm);
+    if (p->eq) plan_free_device(p->eq.get());
+    p->eq.reset();
     fft_plan_free(p->fft);
     p->d_slot_cos = p->d_slot_sin = p->d_slot_chalf = p->d_slot_shalf = nullptr;
     p->d_slot_yn = p->d_slot_ys = nullptr;
-    p->d_coef = nullptr; p->d_fl = nullptr; p->d_coef_ofs = nullptr; p->d_start = nullptr;
+    p->d_coef = p->d_coef2 = nullptr; p->d_fl = nullptr; p->d_coef_ofs = nullptr; p->d_start = nullptr;
     p->d_tile_mlim = nullptr; p->d_synth_items = nullptr; p->d_anal_ms = nullptr;
     p->d_zeros = nullptr;
     p->d_dfac = nullptr;
     p->d_rh = nullptr;
     p->d_phase = nullptr;
+    p->d_slot_scale = nullptr; p->d_band = nullptr; p->d_band_alm = nullptr;
 }
 
 // Algorithmic work of the Legendre step (see sht.h): per kept (m, slot, l)
@@ -106,7 +110,7 @@ static void plan_free_device(Plan *p)
 // 16 (spin s > 0) flops of products; HBM: a_lm + 2 x phases + maps.
 static void count_work(Plan &p)
 {
-    const double triples = count_triples(p.shape(), p.slots, p.slots_per_tile);
+    const double triples = count_triples(p.shape(), p.slots, p.spin ? 32 : 64);
     const double r = p.spin ? 10.0 : 4.0, c = p.spin ? 16.0 : 4.0;
     p.flops_rec = triples * r;
     p.flops_prod = triples * c * p.ntrans;
@@ -134,9 +138,9 @@ int build_synth_items(Plan &p)
         double cost = 0.0;
         for (int m = mb; m < std::min(p.mmax + 1, mb + MB); ++m) {
             const double lrange = (double)(p.lmax + 1 - std::max(m, p.spin));
-            // one item per active slot tile, or (vector path) per group of K
-            // consecutive 64-slot units with an active tile
-            const int tstep = p.tune.valu ? valu_k(p, false) * (64 / p.slots_per_tile) : 1;
+            // one item per active slot tile, or (vector path; spin 0 on the matrix
+            // cores) per group of consecutive tiles with an active one
+            const int tstep = synth_tile_step(p);
             for (int t = 0; t < p.ntiles; t += tstep) {
                 bool act = false;
                 for (int u = t; u < std::min(p.ntiles, t + tstep); ++u) act = act || p.tile_mlim[u] >= m;
@@ -169,51 +173,131 @@ int build_synth_items(Plan &p)
                       "upload");
 }
 
-static int plan_build(Plan &p)
+// slots with sin t below this keep the spin kernels in a plan with a scalar part:
+// the division by sin^s t multiplies the rounding of the spin-0 sums there.
+// Relative rms error of spin-2 maps by ring against long double sums (C_l =
+// 1/(l + 1)^2, lmax 511; spin kernels / scalar part): sin t 0.05-0.1 2.4e-15 /
+// 2.2e-14, 0.1-0.2 1.7e-15 / 5.2e-15, 0.2-0.3 1.3e-15 / 2.1e-15, from 0.3 on equal
+// within 10%; over all rings 2.4e-15 in the spin kernels, and in a plan with the
+// line anywhere from 0.2 to 0.8.
+constexpr double SPLIT_SIN = 0.2;
+
+// A scalar part costs four more launches on the matrix cores (two on the vector
+// units) and a second chain of recursions over l in each direction; it pays from these
+// sizes on, whatever the spin and the direction.
+// Matrix cores, coefficients x slots; transform and inverse on Gauss-Legendre rings,
+// spin 2, spin kernels / scalar part, 4 and 16 transforms: lmax 800 (1.3e8)
+// 978 / 1028, 2879 / 2915 us; 1000 (2.5e8) 1552 / 1556, 4845 / 4437; 1200 (4.3e8)
+// 2198 / 1927, 6595 / 5410; batches of four such plans the same within 5%.
+constexpr int64_t SPLIT_WORK = 330000000;
+// Vector units: where the spin kernels take two slots per lane, that is more than 64
+// slots (one spin-2 transform: lmax 120, 61 slots, 62 / 71 us; 128, 65 slots, 83 / 72).
+constexpr int SPLIT_SLOTS_VALU = 65;
+
+// Number of slots of the plan that keep the spin kernels: all of them, or (spin 1
+// and 2 in FP64, from the sizes above) whole 32-slot tiles from the pole.
+static int split_slots(const Plan &p)
+{
+    const int n = (int)p.slots.size();
+    if (p.precision != SHT_FP64 || (p.spin != 1 && p.spin != 2)) return n;
+    if (default_tuning(p).valu ? n < SPLIT_SLOTS_VALU : p.nalm * n < SPLIT_WORK) return n;
+    int np = 0;
+    while (np < n && p.slots[np].sth < SPLIT_SIN) ++np;
+    np = std::max(32, (np + 15) / 32 * 32);
+    return n - np >= 16 ? np : n;
+}
+
+int ensure_tables(Plan &p, bool valu)
+{
+    const bool two = two_step(p) && !valu;
+    if (two ? p.d_coef2 != nullptr : p.d_coef != nullptr) return SHT_OK;
+    // the m that have an active slot
+    PlanShape shape = p.shape();
+    shape.mmax = std::max(0, p.own_mlim);
+    std::vector<Coef4> coef;
+    std::vector<double> fl;
+    std::vector<int64_t> cofs;
+    if (two) build_coef2(shape, coef, cofs);
+    else build_coef(shape, coef, fl, cofs);
+    static_assert(sizeof(Coef4) == sizeof(double4), "coefficient layout");
+    int rc = SHT_OK;
+    if (!p.d_coef_ofs) {
+        // (m without an active slot: the last row, whose degree range covers
+        // theirs, is read but never used)
+        const int64_t last = cofs.back();
+        cofs.resize(p.mmax + 1, last);
+        if ((rc = dev_alloc((void **)&p.d_coef_ofs, cofs.size() * sizeof(int64_t), "coefficient table"))) return rc;
+        if ((rc = dev_upload(p.d_coef_ofs, cofs.data(), cofs.size() * sizeof(int64_t), "upload"))) return rc;
+    }
+    double4 *d = nullptr;
+    double *f = nullptr;
+    rc = dev_alloc((void **)&d, coef.size() * sizeof(double4), "coefficient table");
+    if (!rc) rc = dev_upload(d, coef.data(), coef.size() * sizeof(double4), "upload");
+    if (!rc && !two) rc = dev_alloc((void **)&f, fl.size() * sizeof(double), "coefficient table");
+    if (!rc && !two) rc = dev_upload(f, fl.data(), fl.size() * sizeof(double), "upload");
+    if (rc) {
+        dev_free(d);
+        dev_free(f);
+        return rc;
+    }
+    if (two) {
+        p.d_coef2 = d;
+    } else {
+        p.d_coef = d;
+        p.d_fl = f;
+    }
+    return SHT_OK;
+}
+
+// Tables of the Legendre kernels over the slots [first, first + p.nslots) of
+// `slots` (sorted pole first).
+static int legendre_build(Plan &p, const std::vector<SlotHost> &slots, int first)
 {
     int rc;
-    build_slots(p.geom, p.slots);
-    p.nslots = (int)p.slots.size();
     p.slots_per_tile = p.spin ? 32 : 64;
     p.ntiles = (p.nslots + p.slots_per_tile - 1) / p.slots_per_tile;
     p.tile_mlim.assign(p.ntiles, -1);
+    PlanShape crit = p.shape();
+    crit.spin = p.crit_spin;
+    crit.lmax = p.crit_lmax;
+    p.own_mlim = -1;
     for (int sl = 0; sl < p.nslots; ++sl) {
         int t = sl / p.slots_per_tile;
-        p.tile_mlim[t] = std::max(p.tile_mlim[t], slot_mlim(p.shape(), p.slots[sl]));
+        p.tile_mlim[t] = std::max(p.tile_mlim[t], slot_mlim(crit, slots[first + sl]));
+        p.own_mlim = std::max(p.own_mlim, std::min(p.mmax, p.tile_mlim[t]));
     }
     // slot tables (padded to whole tiles)
     const int ns = p.ntiles * p.slots_per_tile;
-    std::vector<double> sc(ns, 0.0), ss(ns, 0.0), sch(ns, 1.0), ssh(ns, 0.0);
+    std::vector<double> sc(ns, 0.0), ss(ns, 0.0), sch(ns, 1.0), ssh(ns, 0.0), scale(3 * ns, 0.0);
+    std::fill(scale.begin(), scale.begin() + ns, 1.0);
     std::vector<int> yn(ns, -1), ys(ns, -1);
     for (int i = 0; i < p.nslots; ++i) {
-        sc[i] = p.slots[i].cth; ss[i] = p.slots[i].sth;
-        sch[i] = p.slots[i].chalf; ssh[i] = p.slots[i].shalf;
-        yn[i] = p.slots[i].yn; ys[i] = p.slots[i].ys;
+        const SlotHost &s = slots[first + i];
+        sc[i] = s.cth; ss[i] = s.sth;
+        sch[i] = s.chalf; ssh[i] = s.shalf;
+        yn[i] = s.yn; ys[i] = s.ys;
+        // the phases of a scalar part: over sin^s t (0: crit_spin is the plan's own spin)
+        for (int k = p.spin; k < p.crit_spin; ++k) scale[i] /= s.sth;
+        scale[ns + i] = s.c2;
+        scale[2 * ns + i] = s.s2;
     }
     if ((rc = dev_alloc((void **)&p.d_slot_cos, ns * sizeof(double), "slot tables"))) return rc;
     if ((rc = dev_alloc((void **)&p.d_slot_sin, ns * sizeof(double), "slot tables"))) return rc;
     if ((rc = dev_alloc((void **)&p.d_slot_chalf, ns * sizeof(double), "slot tables"))) return rc;
     if ((rc = dev_alloc((void **)&p.d_slot_shalf, ns * sizeof(double), "slot tables"))) return rc;
+    if ((rc = dev_alloc((void **)&p.d_slot_scale, scale.size() * sizeof(double), "slot tables"))) return rc;
     if ((rc = dev_alloc((void **)&p.d_slot_yn, ns * sizeof(int), "slot tables"))) return rc;
     if ((rc = dev_alloc((void **)&p.d_slot_ys, ns * sizeof(int), "slot tables"))) return rc;
     if ((rc = dev_upload(p.d_slot_cos, sc.data(), ns * sizeof(double), "upload"))) return rc;
     if ((rc = dev_upload(p.d_slot_sin, ss.data(), ns * sizeof(double), "upload"))) return rc;
     if ((rc = dev_upload(p.d_slot_chalf, sch.data(), ns * sizeof(double), "upload"))) return rc;
     if ((rc = dev_upload(p.d_slot_shalf, ssh.data(), ns * sizeof(double), "upload"))) return rc;
+    if ((rc = dev_upload(p.d_slot_scale, scale.data(), scale.size() * sizeof(double), "upload"))) return rc;
     if ((rc = dev_upload(p.d_slot_yn, yn.data(), ns * sizeof(int), "upload"))) return rc;
     if ((rc = dev_upload(p.d_slot_ys, ys.data(), ns * sizeof(int), "upload"))) return rc;
 
-    std::vector<Coef4> coef;
-    std::vector<double> fl;
-    std::vector<int64_t> cofs;
-    build_coef(p.shape(), coef, fl, cofs);
-    static_assert(sizeof(Coef4) == sizeof(double4), "coefficient layout");
-    if ((rc = dev_alloc((void **)&p.d_coef, coef.size() * sizeof(double4), "coefficient table"))) return rc;
-    if ((rc = dev_upload(p.d_coef, coef.data(), coef.size() * sizeof(double4), "upload"))) return rc;
-    if ((rc = dev_alloc((void **)&p.d_fl, fl.size() * sizeof(double), "coefficient table"))) return rc;
-    if ((rc = dev_upload(p.d_fl, fl.data(), fl.size() * sizeof(double), "upload"))) return rc;
-    if ((rc = dev_alloc((void **)&p.d_coef_ofs, cofs.size() * sizeof(int64_t), "coefficient table"))) return rc;
-    if ((rc = dev_upload(p.d_coef_ofs, cofs.data(), cofs.size() * sizeof(int64_t), "upload"))) return rc;
+    p.tune = default_tuning(p);
+    if ((rc = ensure_tables(p, p.tune.valu))) return rc;
 
     std::vector<StartCoef> st;
     build_start(p.shape(), st);
@@ -232,12 +316,60 @@ static int plan_build(Plan &p)
         if ((rc = dev_alloc((void **)&p.d_dfac, df.size() * sizeof(double), "derivative factors"))) return rc;
         if ((rc = dev_upload(p.d_dfac, df.data(), df.size() * sizeof(double), "upload"))) return rc;
     }
-    p.tune = default_tuning(p);
-    if ((rc = build_synth_items(p))) return rc;
-    p.anal_ms.resize(p.mmax + 1);
-    for (int m = 0; m <= p.mmax; ++m) p.anal_ms[m] = m;
+    return build_synth_items(p);
+}
+
+// m values of the analysis launch, 0 .. top, in the order of its work groups:
+// longest degree ranges (small m) first.  Spin 0 in FP64: work group i runs on die i
+// mod NUM_XCD, so within 64 m the die's eight groups take eight consecutive m, whose
+// phases share 128-byte lines, and a line is read into one die's L2 once (32
+// transforms at lmax 4095: 64 -> 28 GB read per launch, 40.0 -> 39.2 ms; the other
+// kernels, whose lines meet in another order, lost 2%).
+static int anal_list_build(Plan &p, int top)
+{
+    p.anal_ms.resize(top + 1);
+    constexpr int B = 8 * NUM_XCD;
+    for (int m = 0; m <= top; ++m) p.anal_ms[m] = m;
+    if (two_step(p))
+        for (int m0 = 0; m0 + B <= top + 1; m0 += B)   // (a last block with fewer m: in order)
+            for (int r = 0; r < B; ++r) p.anal_ms[m0 + r] = m0 + 8 * (r % NUM_XCD) + r / NUM_XCD;
+    int rc;
     if ((rc = dev_alloc((void **)&p.d_anal_ms, p.anal_ms.size() * sizeof(int), "m list"))) return rc;
-    if ((rc = dev_upload(p.d_anal_ms, p.anal_ms.data(), p.anal_ms.size() * sizeof(int), "upload"))) return rc;
+    return dev_upload(p.d_anal_ms, p.anal_ms.data(), p.anal_ms.size() * sizeof(int), "upload");
+}
+
+static int plan_build(Plan &p, bool split)
+{
+    int rc;
+    // (the FP32 form rounds lambda to single precision: its results stay tied to the
+    // colatitudes as given out)
+    build_slots(p.geom, p.slots, p.precision == SHT_FP64);
+    const int nall = (int)p.slots.size();
+    p.nslots = split ? split_slots(p) : nall;
+    p.crit_spin = p.spin;
+    p.crit_lmax = p.lmax;
+    if (p.nslots < nall) {
+        p.eq.reset(new (std::nothrow) Plan());
+        if (!p.eq) { set_error("host allocation failed"); return SHT_ENOMEM; }
+        Plan &e = *p.eq;
+        e.device = p.device;
+        e.lmax = p.lmax + p.spin; e.mmax = p.mmax; e.spin = 0; e.ntrans = p.ncomp * p.ntrans;
+        e.precision = p.precision; e.ncomp = 1;
+        e.geom.nrings = p.geom.nrings;
+        e.polar_T = p.polar_T;
+        e.rescale_bits = p.rescale_bits;
+        e.flush_chunks = p.flush_chunks;
+        e.nalm = sht_nalm(e.lmax, e.mmax);
+        e.crit_spin = p.spin;
+        e.crit_lmax = p.lmax;
+        e.nslots = nall - p.nslots;
+        if ((rc = legendre_build(e, p.slots, p.nslots)) || (rc = anal_list_build(e, e.mmax)) ||
+            (rc = band_upload(p)) ||
+            (rc = dev_alloc((void **)&p.d_band_alm, (size_t)e.ntrans * e.nalm * 16, "scalar coefficients")))
+            return rc;
+    }
+    if ((rc = legendre_build(p, p.slots, 0))) return rc;
+    if ((rc = anal_list_build(p, p.eq ? p.own_mlim : p.mmax))) return rc;
 
     p.phase_elems = (int64_t)p.ntrans * p.ncomp * p.geom.nrings * (p.mmax + 1);
     if ((rc = dev_alloc((void **)&p.d_phase, (size_t)p.phase_elems * 16, "phase workspace"))) return rc;
@@ -250,10 +382,16 @@ static int plan_build(Plan &p)
     return SHT_OK;
 }
 
+int slot_phase_mlim(const Plan &p, int slot)
+{
+    if (slot < p.nslots) return p.tile_mlim[slot / p.slots_per_tile];
+    return p.eq->tile_mlim[(slot - p.nslots) / p.eq->slots_per_tile];
+}
+
 sht_tuning default_tuning(const Plan &p)
 {
     sht_tuning t{};
-    t.synth_ncb = synth_ncb_default(p.spin, p.ntrans, p.precision);
+    t.synth_ncb = synth_ncb_default(p);
     t.synth_mblock = 4;
     t.anal_ncb = anal_ncb(p.spin, p.ntrans);
     t.anal_tpw = anal_tpw_built(p.spin, t.anal_ncb);
@@ -297,13 +435,23 @@ int apply_tuning(Plan &p, const sht_tuning &t)
     int rc = tuning_check(p, t);
     if (rc) return rc;
     const sht_tuning old = p.tune;
-    p.tune = t;
-    if ((rc = build_synth_items(p))) {
-        p.tune = old;
-        (void)build_synth_items(p);
-        return rc;
-    }
-    return SHT_OK;
+    // the scalar part follows the choice of vector or matrix kernels and the m
+    // blocks; its column blocks are its own
+    auto apply = [&](const sht_tuning &c) {
+        int r = ensure_tables(p, c.valu);
+        if (!r && p.eq) r = ensure_tables(*p.eq, c.valu);
+        if (r) return r;
+        p.tune = c;
+        r = build_synth_items(p);
+        if (!r && p.eq) {
+            p.eq->tune.valu = c.valu;
+            p.eq->tune.synth_mblock = c.synth_mblock;
+            r = build_synth_items(*p.eq);
+        }
+        return r;
+    };
+    if ((rc = apply(t))) (void)apply(old);
+    return rc;
 }
 
 LegView make_leg_view(const Plan &p)
@@ -317,10 +465,16 @@ LegView make_leg_view(const Plan &p)
     v.slot_cos = p.d_slot_cos; v.slot_sin = p.d_slot_sin;
     v.slot_chalf = p.d_slot_chalf; v.slot_shalf = p.d_slot_shalf;
     v.slot_yn = p.d_slot_yn; v.slot_ys = p.d_slot_ys;
-    v.coef = p.d_coef; v.fl = p.d_fl; v.coef_ofs = p.d_coef_ofs; v.start = p.d_start;
+    v.coef = p.d_coef; v.coef2 = p.d_coef2; v.fl = p.d_fl; v.coef_ofs = p.d_coef_ofs; v.start = p.d_start;
     v.tile_mlim = p.d_tile_mlim;
     v.zeros = p.d_zeros;
     v.dfac = p.d_dfac;
+    const int64_t ns = (int64_t)p.ntiles * p.slots_per_tile;
+    v.slot_scale = p.d_slot_scale;
+    v.slot_c2 = p.d_slot_scale + ns;
+    v.slot_s2 = p.d_slot_scale + 2 * ns;
+    v.crit_spin = p.crit_spin;
+    v.crit_lmax = p.crit_lmax;
     v.nalm = p.nalm;
     return v;
 }
@@ -437,7 +591,11 @@ int sht_plan_create(const sht_geom *g, int lmax, int mmax, int spin, int ntrans,
     p->real_h = o.real_harmonics != 0;
     p->nalm = sht_nalm(lmax, mmax);
     fault_arm();
-    int rc = plan_build(*p);
+    int rc = plan_build(*p, true);
+    if (rc == SHT_ENOMEM && p->eq) {   // no room for the scalar part: the spin kernels do all slots
+        plan_free_device(p);
+        rc = plan_build(*p, false);
+    }
     if (rc) {
         plan_free_device(p);
         delete p;
@@ -565,9 +723,15 @@ int sht_plan_info(const sht_plan *h, int64_t *n_items, int64_t *device_bytes)
 {
     Plan *p = as_plan(const_cast<sht_plan *>(h));
     if (!p) { set_error("invalid plan handle"); return SHT_ESTATE; }
-    if (n_items) *n_items = p->n_items;
+    if (n_items) *n_items = p->n_items + (p->eq ? p->eq->n_items : 0);
     if (device_bytes) {
-        const void *bufs[] = {p->d_slot_cos, p->d_slot_sin, p->d_slot_chalf, p->d_slot_shalf, p->d_slot_yn,
+        const Plan *e = p->eq.get();
+        const Plan none;
+        if (!e) e = &none;
+        const void *bufs[] = {p->d_coef2, e->d_coef2, p->d_slot_scale, p->d_band, p->d_band_alm, e->d_slot_cos, e->d_slot_sin, e->d_slot_chalf,
+                              e->d_slot_shalf, e->d_slot_scale, e->d_slot_yn, e->d_slot_ys, e->d_coef, e->d_fl,
+                              e->d_coef_ofs, e->d_start, e->d_tile_mlim, e->d_zeros, e->d_dfac, e->d_synth_items,
+                              e->d_anal_ms, p->d_slot_cos, p->d_slot_sin, p->d_slot_chalf, p->d_slot_shalf, p->d_slot_yn,
                               p->d_slot_ys, p->d_coef, p->d_fl, p->d_coef_ofs, p->d_start, p->d_tile_mlim,
                               p->d_zeros, p->d_dfac, p->d_synth_items, p->d_anal_ms, p->d_phase, p->d_rh,
                               p->fft.d_rows, p->fft.d_tw, p->fft.d_perm, p->fft.d_blue, p->fft.d_mvalid,

@@ -4,6 +4,7 @@
 #include <hip/hip_runtime.h>
 
 #include <cstdint>
+#include <memory>
 #include <string>
 #include <vector>
 
@@ -65,11 +66,15 @@ struct LegView {
     const int *slot_yn, *slot_ys;
     const double4 *coef;        // (alpha, beta, delta+, delta-) per (m, l)
     const double *fl;           // f_l per (m, l): lambda = f mu
+    const double4 *coef2;       // spin 0 on the matrix cores: two-step coefficients and f_l per (m, l)
     const int64_t *coef_ofs;    // coef + coef_ofs[m] + l  for l >= l0(m) (same for fl)
     const StartCoef *start;     // [m][chain] chain 0: +s (or 0), chain 1: -s
     const int *tile_mlim;       // per tile: largest m with an active slot (-1: none)
     const double *zeros;        // 2 (lmax + 1) zeros: operand source of unused columns
     const double *dfac;         // sqrt(l (l + 1)), l = 0 .. lmax + 1 (derivative synthesis)
+    const double *slot_c2, *slot_s2;   // cos^2 t, sin^2 t, rounded once (two-step recursion)
+    const double *slot_scale;   // spin-0 kernels: factor of a slot's phases (1, or sin^-s t of a scalar part)
+    double crit_spin, crit_lmax;   // spin and lmax of the polar criterion (the transform's own)
     int64_t nalm;
 };
 
@@ -87,6 +92,8 @@ struct FftPlan {
     size_t table_bytes = 0;
 };
 
+struct BandL;   // per-degree factors of the spin <-> scalar band (spinband.hip)
+
 struct Plan {
     uint64_t serial = 0;             // registry serial of this plan
     uint64_t generation = 0;         // bumped whenever its work lists change (autotuner)
@@ -100,9 +107,19 @@ struct Plan {
     bool real_h = false;             // real spherical harmonics storage
     double *d_rh = nullptr;          // its conversion workspace (coefficients)
     int64_t nalm = 0;
-    // slots
+    // slots: all of them, pole first; the plan's own Legendre kernels run on the
+    // first nslots, the scalar part (if any) on the others
     std::vector<SlotHost> slots;
     int nslots = 0, ntiles = 0, slots_per_tile = 32;
+    int crit_spin = 0, crit_lmax = 0;   // spin and lmax of the polar criterion
+    // scalar part of a spin-1 or spin-2 plan (spinband.hip): a plan of spin 0,
+    // ncomp * ntrans transforms and band limit lmax + spin on the slots away from
+    // the poles, its coefficient workspace and the per-degree band factors
+    std::unique_ptr<Plan> eq;
+    double *d_band_alm = nullptr;
+    BandL *d_band = nullptr;
+    double *d_slot_scale = nullptr;  // per slot: [0, n) factor, [n, 2 n) cos^2 t, [2 n, 3 n) sin^2 t (n padded)
+    int own_mlim = -1;               // largest m with an active slot among the plan's own
     std::vector<int> tile_mlim;
     // host-side work lists
     std::vector<WaveItem> synth_items;
@@ -112,7 +129,8 @@ struct Plan {
     double *d_slot_cos = nullptr, *d_slot_sin = nullptr, *d_slot_chalf = nullptr,
            *d_slot_shalf = nullptr;
     int *d_slot_yn = nullptr, *d_slot_ys = nullptr;
-    double4 *d_coef = nullptr;
+    double4 *d_coef = nullptr;       // with d_fl: one-step tables
+    double4 *d_coef2 = nullptr;      // two-step table (built where the kernels in use read it)
     double *d_fl = nullptr;
     int64_t *d_coef_ofs = nullptr;
     StartCoef *d_start = nullptr;
@@ -184,10 +202,14 @@ struct Batch {
 };
 
 LegView make_leg_view(const Plan &p);
+// largest m whose phase entry the Legendre kernels handle at this slot (its tile's limit)
+int slot_phase_mlim(const Plan &p, int slot);
 
 // Legendre step launchers (legendre.hip)
 int launch_legendre_synth(const Plan &p, const double *alm, double *phase, bool deriv, hipStream_t s);
-int synth_ncb_default(int spin, int ntrans, int precision);
+int synth_ncb_default(const Plan &p);
+int synth0_ncb(const Plan &p);
+int anal0_batch_ncb(const Batch &b);
 int build_synth_items(Plan &p);
 // tuning: defaults for a plan, validity (SHT_OK or SHT_EUNSUPPORTED with a
 // message), and applying one (rebuilds the work lists, bumps the generation)
@@ -195,6 +217,7 @@ sht_tuning default_tuning(const Plan &p);
 int tuning_check(const Plan &p, const sht_tuning &t);
 int apply_tuning(Plan &p, const sht_tuning &t);
 int anal_tpw_built(int spin, int ncb);   // tiles per wavefront of the built analysis kernels
+int synth_tile_step(const Plan &p);      // slot tiles per synthesis work item
 int valu_jpg(const Plan &p);             // transforms per work item of the vector-unit kernels
 int valu_k(const Plan &p, bool anal);    // slot tiles per lane group of the vector-unit kernels
 int launch_legendre_anal(const Plan &p, const double *phase, double *alm, int mode, hipStream_t s);
@@ -208,6 +231,18 @@ int synth_batch_groups(int spin, int ncb, bool f32, int device);
 int anal_batch_groups(int spin, int ncb, bool f32, int device);
 int anal_ncb(int spin, int ntrans);
 
+// spin-0 FP64 matrix-core kernels (legendre0.hip)
+int launch_legendre_synth0(const Plan &p, const double *alm, double *phase, hipStream_t s);
+int launch_legendre_anal0(const Plan &p, const double *phase, double *alm, int mode, hipStream_t s);
+int anal0_batch_groups(int ncb, int device);
+int synth0_batch_groups(int ncb, int device);
+void launch_anal0_batch(const Batch &b, const BatchPtrs &ptrs, int mode, hipStream_t s);
+void launch_synth0_batch(const Batch &b, const BatchPtrs &ptrs, const SynQueues &q, unsigned *counters, hipStream_t s);
+// whether the plan's matrix-core kernels are those (two-step table)
+inline bool two_step(const Plan &p) { return p.spin == 0 && p.precision == SHT_FP64; }
+// recursion tables of the vector-unit (valu) or matrix-core kernels, built if missing
+int ensure_tables(Plan &p, bool valu);
+
 // ring FFT (ringfft.hip)
 int fft_plan_build(Plan &p);
 void fft_plan_free(FftPlan &f);
@@ -215,6 +250,13 @@ int launch_ring_synth(const Plan &p, const double *phase, double *map, bool use_
 int launch_ring_anal(const Plan &p, const double *map, double *phase, bool use_weights,
                      hipStream_t s);
 int launch_phase_tail_zero(const Plan &p, double *phase, hipStream_t s);
+
+// scalar part of spin-1 and spin-2 plans (spinband.hip): per-degree factors of
+// the band (host table of lmax + 2 spin + 2 entries), and the banded maps between
+// the plan's coefficients and the scalar part's
+int band_upload(Plan &p);
+int launch_band_synth(const Plan &p, const double *alm, double *q, bool deriv, hipStream_t s);
+int launch_band_anal(const Plan &p, const double *q, double *alm, int mode, hipStream_t s);
 
 // real spherical harmonics storage <-> complex a_lm (realharm.hip)
 int launch_real_harm(const Plan &p, const double *in, double *out, int ncomp, bool to_complex, hipStream_t s);
