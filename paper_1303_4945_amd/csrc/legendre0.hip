@@ -328,9 +328,11 @@ __global__ __launch_bounds__(64 * NW, 4) void k_legendre_synth0(LegView v, const
 // output of a chunk follow each other between barriers, all wavefronts in step: the
 // matrix instructions then meet no vector instructions of a neighbour (each waits
 // for a matrix instruction to end).  The 64-slot partial sums are added in a fixed
-// order, (P0 + P1) + (P2 + P3), so the result does not depend on NCB; the totals
-// times f_l are added to a_lm by the wavefronts of the first share (a lane holds
-// four columns of one degree).  256 slots per pass keep the read-modify-write of
+// order, (P0 + P1) + (P2 + P3), so the result does not depend on NCB; a lane holds
+// four columns of one degree, and each share adds the totals of its NCB of them,
+// times f_l, to a_lm, whose earlier value it loads before the recursion (8
+// transforms at lmax 4096 on HEALPix N_side 2048, NCB = 1: 27.5 ms with all of it in
+// the first share and the load after the products, 24.9 so).  256 slots per pass keep the read-modify-write of
 // a_lm at 1/16 of the bytes that 16 slots would take.  Measured, sixteen spin-2
 // transforms at lmax 4095 (64 scalar columns): 42.2 ms in the one-step kernel of 64
 // slots x 16 columns on the same slots, 39.2 here; a chunk takes 13.3-14.6k cycles, of
@@ -350,12 +352,12 @@ constexpr int a0_lrow() { return NCB == 1 ? 33 : 34; }
 
 template <int NCB>
 struct Ana0Shared {
-    static constexpr int NPART = NCB == 4 ? 1 : NCB == 2 ? 4 : 6;   // wavefronts beyond the first share
+    static constexpr int NR = NCB;                  // columns of a lane that its wavefront sums up and puts out
     union {
         double lam[8][A0_LC * a0_lrow<NCB>()];      // region: [class * 16 + degree / 2][slot]
         double g[2][128 * 16 * NCB];                // phases of a class on their way to the registers
     };
-    double part[NPART][NCB == 4 ? 1 : 256];
+    double part[NCB == 4 ? 1 : A0_NW][4 - NR ? 4 - NR : 1][64];   // the others, on their way to the other shares
     double4 cf[A0_LC];
     double f[2][A0_LC];
     int on[8];                                      // the region's lambda is not all zero in the chunk
@@ -381,10 +383,11 @@ __device__ __forceinline__ void anal0_item(const LegView &v, const int m, const 
     const double fac = ((mode & ANA_MODE_GRAD) && m > 0) ? 2.0 : 1.0;   // fac_m of the real-field gradient
     const int rpar = lane >> 5, rslot = lane & 31;                      // recursion role
 
-    // output elements of a share-0 wavefront: columns 16 cb + kk + 4 r (transform
-    // ot + 2 r), degree lc + par + 2 i16
-    const int ot = t0 + 8 * cb + (kk >> 1);
-    const int nout = share ? 0 : (v.ntrans - ot + 1) / 2;   // r < nout: the transform exists
+    // a lane's sums: columns 16 cb + kk + 4 r, r < 4 (transform t0 + 8 cb + kk / 2 + 2 r),
+    // degree lc + par + 2 i16; this share puts out NR of them from r0 on
+    constexpr int NR = Ana0Shared<NCB>::NR;
+    const int r0 = share * NR, ot = t0 + 8 * cb + (kk >> 1) + 2 * r0;
+    const int nout = (v.ntrans - ot + 1) / 2;               // r < nout: the transform exists
     double *const obase = alm + ((int64_t)(ot < v.ntrans ? ot : 0) * v.nalm + mbase) * 2 + (kk & 1);
     const int64_t ostride = 4 * v.nalm;
     const bool imz = m == 0 && (kk & 1);                    // Im a_l0
@@ -496,16 +499,12 @@ __device__ __forceinline__ void anal0_item(const LegView &v, const int m, const 
         int c = 0;
         for (int lc = m; lc <= lmax; lc += LC, ++c) {
             fetch(lc + LC);
-            // the earlier passes' sums: in flight during the products where the
-            // registers allow, else loaded after them
+            // the earlier passes' sums: in flight during recursion and products
             const int ol = lc + par + 2 * i16;
             double *const o = obase + 2 * (int64_t)(ol > lmax ? lmax : ol);
-            double prev[4];
-            auto earlier = [&]() {
+            double prev[NR];
 #pragma unroll
-                for (int r = 0; r < 4; ++r) prev[r] = !first && r < nout ? o[r * ostride] : 0.0;
-            };
-            if constexpr (NCB == 4) earlier();
+            for (int r = 0; r < NR; ++r) prev[r] = !first && r < nout ? o[r * ostride] : 0.0;
             if (ract) chain2_chunk<LC / 2, NCB == 4 ? 4 : 2>(cs, pole, slow, &sh.cf[rpar], thr, down, lout, LROW);
             const bool any = ract && chain2_done(cs, live, slow);
             if (lane == 0) sh.on[wave] = any ? 1 : 0;
@@ -517,24 +516,34 @@ __device__ __forceinline__ void anal0_item(const LegView &v, const int m, const 
             dv4 sum = acc[0];
             if constexpr (NQ >= 2) sum = acc[0] + acc[1];
             if constexpr (NQ == 4) sum = sum + (acc[2] + acc[3]);
-            if constexpr (NCB < 4) {
-                earlier();
-                if (share > 0) {
-                    double *pt = sh.part[wave - 2 * NCB];
+            double mine[NR];   // sum[r0 + r]
 #pragma unroll
-                    for (int r = 0; r < 4; ++r) pt[r * 64 + lane] = sum[r];
-                }
+            for (int r = 0; r < NR; ++r) {
+                mine[r] = sum[r];
+#pragma unroll
+                for (int h = 1; h < 4 / NR; ++h) mine[r] = share == h ? sum[h * NR + r] : mine[r];
+            }
+            if constexpr (NR < 4) {
+#pragma unroll
+                for (int r = 0; r < 4; ++r)
+                    if (r / NR != share) sh.part[wave][r < r0 ? r : r - NR][lane] = sum[r];
             }
             __syncthreads();
-            if (share == 0 && ol <= lmax) {
+            if (ol <= lmax) {
                 const double f = sh.f[c & 1][par + 2 * i16];
 #pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    double s = sum[r];
-                    if constexpr (NCB == 2) s += sh.part[wave][r * 64 + lane];
-                    if constexpr (NCB == 1)
-                        s = (s + sh.part[wave][r * 64 + lane]) +
-                            (sh.part[wave + 2][r * 64 + lane] + sh.part[wave + 4][r * 64 + lane]);
+                for (int r = 0; r < NR; ++r) {
+                    double s = mine[r];
+                    if constexpr (NR < 4) {
+                        double ps[4 / NR];
+#pragma unroll
+                        for (int h = 0; h < 4 / NR; ++h) {   // (its own place in part: not written, not used)
+                            const double x = sh.part[par + 2 * (cb + NCB * h)][h < share ? r0 - NR + r : r0 % (4 - NR) + r][lane];
+                            ps[h] = h == share ? mine[r] : x;
+                        }
+                        s = ps[0] + ps[1];
+                        if constexpr (NR == 1) s += ps[2] + ps[3];
+                    }
                     s = first ? f * s : fma(f, s, prev[r]);
                     if (imz) s = 0.0;
                     if (r < nout) o[r * ostride] = s;
