@@ -11,7 +11,7 @@ CSRC = os.path.join(HERE, "csrc")
 BUILD = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libsht.so")
 
-SOURCES = ["host.cpp", "sht_api.cpp", "legendre.hip", "legendre0.hip", "ringfft.hip", "realharm.hip", "spinband.hip", "batch.cpp", "noalloc.hip"]
+SOURCES = ["host.cpp", "sht_api.cpp", "legendre.hip", "legendre0.hip", "legendre_spin.hip", "ringfft.hip", "realharm.hip", "spinband.hip", "batch.cpp", "noalloc.hip"]
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 ARCH = "gfx950"

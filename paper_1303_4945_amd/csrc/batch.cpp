@@ -104,7 +104,7 @@ void synth_queue(Batch &b, std::vector<BatchSynItem> &q)
             Block blk;
             for (int m = m0; m <= std::min(mend, m0 + MB - 1); ++m) {
                 const int m2 = pairs ? p.mmax - m : -1;
-                const int step = synth_tile_step(p);
+                const int step = batch_tile_step(p);
                 for (int t = 0; t < p.ntiles; t += step) {
                     int lim = -1;
                     for (int u = t; u < std::min(p.ntiles, t + step); ++u) lim = std::max(lim, p.tile_mlim[u]);

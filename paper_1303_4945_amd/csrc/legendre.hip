@@ -141,9 +141,6 @@ __device__ __forceinline__ void chain_chunk_fast(Chain &c, const double4 *__rest
     }
 }
 
-// wavefronts with a slot of cos t above this use the difference form
-constexpr double DIFF_FORM_COS = 0.7;
-
 // ---------------------------------------------------------------- synthesis
 
 constexpr int SYN_LC = 16;          // degrees per chunk
@@ -1896,9 +1893,10 @@ static int dispatch_synth(const Plan &p, const LegView &v, const double *alm, do
         else if (ncb == 2) launch_synth_t<0, 2, F32>(p, v, alm, phase, 0, s);
         else return SHT_EINVAL;
     } else {
-        if (ncb == 1) launch_synth_t<2, 1, F32>(p, v, alm, phase, deriv, s);
-        else if (ncb == 2) launch_synth_t<2, 2, F32>(p, v, alm, phase, deriv, s);
-        else return SHT_EINVAL;
+        if constexpr (!F32) {   // (the rest: launch_legendre_synth_spin)
+            if (ncb == 2) launch_synth_t<2, 2, false>(p, v, alm, phase, deriv, s);
+            else return SHT_EINVAL;
+        }
     }
     return SHT_OK;
 }
@@ -1937,10 +1935,17 @@ int valu_k(const Plan &p, bool anal)
     return k < kmax ? k : kmax;
 }
 
+// slot tiles per work item of the batches' persistent synthesis
+int batch_tile_step(const Plan &p)
+{
+    return two_step(p) ? 2 : 1;   // two-step kernels: work groups of up to four 32-slot wavefronts
+}
+
 int synth_tile_step(const Plan &p)
 {
     if (p.tune.valu) return valu_k(p, false) * (64 / p.slots_per_tile);
-    return two_step(p) ? 2 : 1;   // work groups of up to four 32-slot wavefronts
+    if (p.spin) return std::max(1, synth_spin_waves(p));   // wavefronts of one 32-slot tile each
+    return batch_tile_step(p);
 }
 
 template <int J, int K>
@@ -2053,6 +2058,7 @@ int launch_legendre_synth(const Plan &p, const double *alm, double *phase, bool 
         return check_hip(hipGetLastError(), "legendre synthesis launch");
     }
     const int d = deriv ? 1 : 0;
+    if (p.spin && synth_spin_waves(p)) return launch_legendre_synth_spin(p, alm, phase, d, s);
     const int rc = p.precision == SHT_FP32_MFMA ? dispatch_synth<true>(p, v, alm, phase, d, s)
                                                 : dispatch_synth<false>(p, v, alm, phase, d, s);
     if (rc) {

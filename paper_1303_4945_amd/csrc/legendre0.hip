@@ -142,8 +142,6 @@ __device__ __forceinline__ bool chain2_done(const Chain2 &c, bool live, bool &sl
 
 __device__ __forceinline__ double4 chain2_coef(const double4 q) { return double4{q.x, q.y, q.z, q.x}; }
 
-__device__ __forceinline__ bool not_finite(double x) { return !(fabs(x) < __builtin_inf()); }
-
 // ---------------------------------------------------------------- synthesis
 //
 // Work group = (m, 32 NW slots from tile it.tile, 16 NCB columns (8 NCB

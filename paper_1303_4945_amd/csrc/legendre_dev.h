@@ -114,6 +114,11 @@ __device__ inline Chain chain_init(const LegView &v, int m, int slot, int chain)
     return c;
 }
 
+// wavefronts with a slot of cos t above this use the difference form
+constexpr double DIFF_FORM_COS = 0.7;
+
+__device__ __forceinline__ bool not_finite(double x) { return !(fabs(x) < __builtin_inf()); }
+
 __device__ __forceinline__ bool wave_any(bool p)
 {
     return __builtin_amdgcn_ballot_w64(p) != 0;

@@ -208,6 +208,8 @@ int slot_phase_mlim(const Plan &p, int slot);
 // Legendre step launchers (legendre.hip)
 int launch_legendre_synth(const Plan &p, const double *alm, double *phase, bool deriv, hipStream_t s);
 int synth_ncb_default(const Plan &p);
+int launch_legendre_synth_spin(const Plan &p, const double *alm, double *phase, int deriv, hipStream_t s);
+int synth_spin_waves(const Plan &p);
 int synth0_ncb(const Plan &p);
 int anal0_batch_ncb(const Batch &b);
 int build_synth_items(Plan &p);
@@ -217,6 +219,7 @@ sht_tuning default_tuning(const Plan &p);
 int tuning_check(const Plan &p, const sht_tuning &t);
 int apply_tuning(Plan &p, const sht_tuning &t);
 int anal_tpw_built(int spin, int ncb);   // tiles per wavefront of the built analysis kernels
+int batch_tile_step(const Plan &p);
 int synth_tile_step(const Plan &p);      // slot tiles per synthesis work item
 int valu_jpg(const Plan &p);             // transforms per work item of the vector-unit kernels
 int valu_k(const Plan &p, bool anal);    // slot tiles per lane group of the vector-unit kernels
