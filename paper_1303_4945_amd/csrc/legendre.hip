@@ -43,102 +43,11 @@
 namespace sht {
 
 // Per-chain step coefficients of one degree, staged in LDS:
-// (alpha_l, +-beta_l, alpha_l +- beta_l - 2, scale * f_l) for the chain's sign;
-// the last entry turns mu into the value written out (lambda times a constant).
-__device__ inline double4 chain_coef(const double4 c, bool minus, double fs)
+// (alpha_l, +-beta_l, alpha_l +- beta_l - 2, last) for the chain's sign (last:
+// alpha_l again where chain_run reads them in pairs).
+__device__ inline double4 chain_coef(const double4 c, bool minus, double last)
 {
-    return minus ? double4{c.x, -c.y, c.w, fs} : double4{c.x, c.y, c.z, fs};
-}
-
-// Run the recursion over the degrees lc .. lc+LC-1, writing mu (SCALE: times
-// cf.w, i.e. c f_l mu = c lambda) to out[row(t) * stride]; 0 while the lane's
-// scale k < 0 and outside [l0, lmax].  Without SCALE the caller applies f_l on
-// the side of the product with fewer values per degree.
-// Row of degree offset t in the chunk: natural order, or (PSPLIT) the even
-// offsets first and then the odd ones.
-template <int LC, bool PSPLIT>
-__device__ __forceinline__ int chunk_row(int t)
-{
-    return PSPLIT ? (t & 1) * (LC / 2) + (t >> 1) : t;
-}
-
-template <typename T, int LC, bool PSPLIT, bool SCALE>
-__device__ inline void chain_chunk(Chain &c, const double4 *__restrict__ cf, bool diff, bool slow,
-                                   int l0, int lc, int lmax, T *out, int stride, double thr,
-                                   double down)
-{
-    if (!slow) {
-#pragma unroll 4
-        for (int t = 0; t < LC; ++t) {
-            const int l = lc + t;
-            out[chunk_row<LC, PSPLIT>(t) * stride] =
-                (l >= l0 && l <= lmax) ? (T)(SCALE ? c.mu * cf[t].w : c.mu) : (T)0;
-            if (l >= l0 && l < lmax) {
-                const double4 q = cf[t];
-                if (diff) {
-                    const double eps = fma(q.x, c.ms2, q.z);
-                    c.aux = fma(eps, c.mu, c.aux);
-                    c.mu += c.aux;
-                } else {
-                    const double tt = fma(q.x, c.x, q.y);
-                    const double nx = fma(tt, c.mu, -c.aux);
-                    c.aux = c.mu;
-                    c.mu = nx;
-                }
-            }
-        }
-    } else {
-        for (int t = 0; t < LC; ++t) {
-            const int l = lc + t;
-            out[chunk_row<LC, PSPLIT>(t) * stride] =
-                (l >= l0 && l <= lmax && c.k == 0) ? (T)(SCALE ? c.mu * cf[t].w : c.mu) : (T)0;
-            if (l >= l0 && l < lmax) {
-                const double4 q = cf[t];
-                if (diff) {
-                    const double eps = fma(q.x, c.ms2, q.z);
-                    c.aux = fma(eps, c.mu, c.aux);
-                    c.mu += c.aux;
-                } else {
-                    const double tt = fma(q.x, c.x, q.y);
-                    const double nx = fma(tt, c.mu, -c.aux);
-                    c.aux = c.mu;
-                    c.mu = nx;
-                }
-                if (c.k < 0 && fabs(c.mu) >= thr) {
-                    c.mu *= down;
-                    c.aux *= down;
-                    c.k += 1;
-                }
-            }
-        }
-    }
-}
-
-// Fast path of chain_chunk: every degree of the chunk lies in [l0, lmax) and
-// every lane of the wavefront already has k = 0 (no masking, no rescaling).
-template <typename T, int LC, bool PSPLIT, bool SCALE>
-__device__ __forceinline__ void chain_chunk_fast(Chain &c, const double4 *__restrict__ cf, bool diff,
-                                                 T *out, int stride)
-{
-    if (diff) {
-#pragma unroll
-        for (int t = 0; t < LC; ++t) {
-            const double4 q = cf[t];
-            out[chunk_row<LC, PSPLIT>(t) * stride] = (T)(SCALE ? c.mu * q.w : c.mu);
-            const double eps = fma(q.x, c.ms2, q.z);
-            c.aux = fma(eps, c.mu, c.aux);
-            c.mu += c.aux;
-        }
-    } else {
-#pragma unroll
-        for (int t = 0; t < LC; ++t) {
-            const double4 q = cf[t];
-            out[chunk_row<LC, PSPLIT>(t) * stride] = (T)(SCALE ? c.mu * q.w : c.mu);
-            const double nx = fma(fma(q.x, c.x, q.y), c.mu, -c.aux);
-            c.aux = c.mu;
-            c.mu = nx;
-        }
-    }
+    return minus ? double4{c.x, -c.y, c.w, last} : double4{c.x, c.y, c.z, last};
 }
 
 // ---------------------------------------------------------------- synthesis
@@ -184,6 +93,7 @@ template <int SPIN, bool F32>
 struct SynShared {
     typename MT<F32>::T lam[SYN_LC][SYN_ROW];
     double4 cfs[2][SPIN ? 2 : 1][SYN_LC];
+    double f[2][SYN_LC];   // c f_l
 };
 
 template <int SPIN, int NCB, bool F32>
@@ -292,16 +202,17 @@ __device__ __forceinline__ void synth_item(const LegView &v, const WaveItem it,
         const double4 c = (l >= l0 && l < lmax) ? c0n : double4{0, 0, 0, 0};
         const double kd = deriv ? v.dfac[l <= lmax ? l : lmax] : 1.0;
         const double f = (l >= l0 && l <= lmax) ? f0n * fscale * kd : 0.0;
-        if (lane < NCH * LC) cfs[buf][lane / LC][lane % LC] = chain_coef(c, lane >= LC, f);
+        if (lane < NCH * LC) cfs[buf][lane / LC][lane % LC] = chain_coef(c, lane >= LC, c.x);
+        if (lane < LC) sh.f[buf][lane] = f;
     };
-    // c f_l onto the coefficients of the chunk staged in cfs[buf] (zero outside
+    // c f_l onto the coefficients of the chunk staged in buf (zero outside
     // [l0, lmax]): the recursion then writes plain mu
     auto scaleB = [&](int buf, double (&dst)[2][2][NCB]) {
 #pragma unroll
         for (int h = 0; h < 2; ++h)
 #pragma unroll
             for (int par = 0; par < 2; ++par) {
-                const double f0 = cfs[buf][0][8 * h + 2 * kk + par].w;
+                const double f0 = sh.f[buf][8 * h + 2 * kk + par];
                 const double f = tneg ? -f0 : f0;
 #pragma unroll
                 for (int cb = 0; cb < NCB; ++cb) dst[par][h][cb] *= f;
@@ -341,15 +252,28 @@ __device__ __forceinline__ void synth_item(const LegView &v, const WaveItem it,
             loadC(lc + LC);
         }
         T *out = &lam[0][lane];
-        if (!slow && lc >= l0 && lc + LC <= lmax) {
-            chain_chunk_fast<T, LC, false, false>(cs, cfs[buf][rchain], diff, out, SYN_ROW);
-        } else {
-            chain_chunk<T, LC, false, false>(cs, cfs[buf][rchain], diff, slow, l0, lc, lmax, out, SYN_ROW, thr,
-                                            down);
+        const double4 *cf = cfs[buf][rchain];
+        const bool before = lc < l0;
+        bool now = true;   // lambda not all zero, or a coefficient Inf or NaN
+        if (slow || before) {
+            if (diff) chain_run<LC, false, true, true>(cs, cf, before, thr, down, out, SYN_ROW);
+            else chain_run<LC, false, false, true>(cs, cf, before, thr, down, out, SYN_ROW);
             slow = wave_any(cs.k < 0);
+            now = wave_any(cs.k == 0 && (cs.mu != 0.0 || cs.aux != 0.0));
+            if (!now) {
+                bool bad = false;
+#pragma unroll
+                for (int e = 0; e < 4 * NCB; ++e) bad = bad || not_finite((T)R[e & 1][(e >> 1) & 1][e >> 2]);
+                now = wave_any(bad);
+            }
+        } else if (diff) {
+            chain_run<LC, false, true, false>(cs, cf, false, thr, down, out, SYN_ROW);
+        } else {
+            chain_run<LC, false, false, false>(cs, cf, false, thr, down, out, SYN_ROW);
         }
         __syncthreads();
-        if constexpr (SPIN == 0) {
+        if (!now) {
+        } else if constexpr (SPIN == 0) {
 #pragma unroll
             for (int h = 0; h < 2; ++h) {
                 T b0[NCB], b1[NCB];
@@ -495,7 +419,15 @@ constexpr int ana_tpw() { return (SPIN == 0 && NCB == 2) ? 1 : 2; }
 // region, and after one work-group barrier the partial sums of the wavefronts
 // are added in a fixed order and accumulated into a_lm (deterministic, no
 // atomics).  Every pass over the tiles reads and writes the m's a_lm once, so
-// TPW > 1 divides that traffic by TPW at the cost of registers.
+// TPW > 1 divides that traffic by TPW at the cost of registers.  What bounds it: up to
+// about lmax 500 the latency of a chunk (the recursion's steps, whose coefficients come
+// from LDS two steps ahead; the read of the earlier sums, ahead of the recursion where
+// the registers allow), then the matrix cores.  A tile whose lambda underflow through a
+// chunk takes no products.  With the coefficients read where they are used, the earlier
+// sums after the products and every product taken, before / now: spin 3, lmax 511, 4
+// transforms 161 / 124 us; lmax 1500, 16 transforms 5765 / 5217; FP32 products, spin
+// 2, 16 transforms at lmax 2047 8.78 / 7.8 ms; FP32 spin 0, lmax 511, 16 transforms
+// 165 / 134 us.
 template <int SPIN, bool F32>
 struct AnaShape {
     static constexpr int SPT = SPIN ? 32 : 64;
@@ -649,6 +581,7 @@ __device__ __forceinline__ void anal_item(const LegView &v, const int m, const i
         T gw[TPW][2][KSA][NCB];
         Chain cs[TPW];
         bool diff[TPW], slow[TPW];
+        bool nonfin = false;
 #pragma unroll
         for (int i = 0; i < TPW; ++i) {
             const bool active = ptile[i] >= 0;
@@ -682,6 +615,7 @@ __device__ __forceinline__ void anal_item(const LegView &v, const int m, const i
                     const double sg = SPIN ? ((o == 3) ? 1.0 : -1.0) : scv[SPIN ? 0 : ks];   // -tau_o (spin > 0)
                     gw[i][0][ks][cb] = (T)(sg * (gn + gs));
                     gw[i][1][ks][cb] = (T)(sg * (gn - gs));
+                    nonfin = nonfin || not_finite(gw[i][0][ks][cb]) || not_finite(gw[i][1][ks][cb]);
                 }
             }
             cs[i] = chain_init(v, m, active ? ptile[i] * SPT + rslot : v.nslots, rchain);
@@ -689,6 +623,7 @@ __device__ __forceinline__ void anal_item(const LegView &v, const int m, const i
             if (diff[i]) cs[i].aux = cs[i].mu;
             slow[i] = wave_any(cs[i].k < 0);
         }
+        const bool force = wave_any(nonfin);     // an Inf or NaN: no chunk is left out
         const bool any_active = ptile[0] >= 0;   // tiles are dealt to slot 0 first
         // step coefficients of this lane's (chain, degree) entry, loaded one
         // chunk ahead from a clamped address and masked when staged
@@ -699,6 +634,18 @@ __device__ __forceinline__ void anal_item(const LegView &v, const int m, const i
             const int lcl = l < l0 ? l0 : (l > lmax ? lmax : l);
             c0n = coef[lcl];
             f0n = flm[lcl];
+        };
+        // the previous passes' sums of this thread's outputs
+        constexpr bool EARLY = SPIN && (NCB == 1 || F32);
+        auto earlier = [&](int lc, double (&pold)[OPT]) {
+            if (first) return;
+#pragma unroll
+            for (int j = 0; j < OPT; ++j) {
+                const int l = lc + oloff;
+                const int lcl = l < l0 ? l0 : (l > lmax ? lmax : l);
+                const double *src = ((ovalid >> j) & 1) ? obase + j * ostride : alm;
+                pold[j] = src[2 * (int64_t)lcl];   // used only where l is in range
+            }
         };
         loadC(lstart);
         for (int lc = lstart; lc <= lmax; lc += LC) {
@@ -714,22 +661,31 @@ __device__ __forceinline__ void anal_item(const LegView &v, const int m, const i
                 if (wave == 0 && lane < LC) sh.fls[PSEP ? (cidx & 1) : 0][lane] = f;
                 if (any_active) {
                     const double4 c = (l >= l0 && l < lmax) ? c0n : double4{0, 0, 0, 0};
-                    if (lane < NCH * LC) cfs[wave][lane / LC][lane % LC] = chain_coef(c, lane >= LC, f);
+                    if (lane < NCH * LC) cfs[wave][lane / LC][lane % LC] = chain_coef(c, lane >= LC, c.x);
                 }
             }
+            double pold[OPT];   // (where the registers allow, in flight during recursion and products)
+            if constexpr (EARLY) earlier(lc, pold);
             if (lc + LC <= lmax) loadC(lc + LC);
 #pragma unroll
             for (int i = 0; i < TPW; ++i) {
                 if (ptile[i] < 0) continue;
                 wave_sync();
-                if (!slow[i] && lc >= l0 && lc + LC <= lmax) {
-                    chain_chunk_fast<T, LC, true, false>(cs[i], cfs[wave][rchain], diff[i], lam_out, LDP);
-                } else {
-                    chain_chunk<T, LC, true, false>(cs[i], cfs[wave][rchain], diff[i], slow[i], l0, lc, lmax,
-                                                    lam_out, LDP, thr, down);
+                const double4 *cf = cfs[wave][rchain];
+                const bool before = lc < l0;
+                bool now = true;   // lambda not all zero (or a phase Inf or NaN)
+                if (slow[i] || before) {
+                    if (diff[i]) chain_run<LC, true, true, true>(cs[i], cf, before, thr, down, lam_out, LDP);
+                    else chain_run<LC, true, false, true>(cs[i], cf, before, thr, down, lam_out, LDP);
                     slow[i] = wave_any(cs[i].k < 0);
+                    now = force || wave_any(cs[i].k == 0 && (cs[i].mu != 0.0 || cs[i].aux != 0.0));
+                } else if (diff[i]) {
+                    chain_run<LC, true, true, false>(cs[i], cf, false, thr, down, lam_out, LDP);
+                } else {
+                    chain_run<LC, true, false, false>(cs[i], cf, false, thr, down, lam_out, LDP);
                 }
                 wave_sync();
+                if (!now) continue;
 #pragma unroll
                 for (int p = 0; p < 2; ++p) {
 #pragma unroll
@@ -754,18 +710,7 @@ __device__ __forceinline__ void anal_item(const LegView &v, const int m, const i
                 }
                 wave_sync();   // lambda reads issued: the region takes the next tile or the partial sums
             }
-            // the previous passes' sums of this thread's outputs (loaded after the
-            // products, so that they take no registers during them)
-            double pold[OPT];
-            if (!first) {
-#pragma unroll
-                for (int j = 0; j < OPT; ++j) {
-                    const int l = lc + oloff;
-                    const int lcl = l < l0 ? l0 : (l > lmax ? lmax : l);
-                    const double *src = ((ovalid >> j) & 1) ? obase + j * ostride : alm;
-                    pold[j] = src[2 * (int64_t)lcl];   // used only where l is in range
-                }
-            }
+            if constexpr (!EARLY) earlier(lc, pold);
 #pragma unroll
             for (int p = 0; p < 2; ++p)
 #pragma unroll

@@ -149,4 +149,60 @@ inline int persistent_groups(K kernel, int threads, int dev)
     return g > 0 ? g : 1024;
 }
 
+// Row of degree offset t in a chunk: natural order, or (PSPLIT) the even offsets
+// first and then the odd ones.
+template <int LC, bool PSPLIT>
+__device__ __forceinline__ int chunk_row(int t)
+{
+    return PSPLIT ? (t & 1) * (LC / 2) + (t >> 1) : t;
+}
+
+// A chunk of the one-step recursion, mu to out[row(t) stride]; cf: per degree alpha,
+// beta, the difference form's constant, alpha.  GEN: before (degree offset 0 lies below
+// l0: no output, no step) and lanes whose scale is below 0 (no output; rescaled).  The
+// coefficients of two steps are read together, one pair ahead of their use: read where
+// they are used, every step would wait for the LDS (130 cycles against the 24 of its
+// arithmetic).  The degrees past lmax, with coefficients 0, write finite values that
+// the caller does not use.
+template <int LC, bool PSPLIT, bool DIFF, bool GEN, typename T>
+__device__ __forceinline__ void chain_run(Chain &c, const double4 *cf, bool before, double thr, double down, T *out,
+                                          int stride)
+{
+    const double *q0 = reinterpret_cast<const double *>(cf) + (DIFF ? 2 : 0);
+    double2 q[2][2];
+#pragma unroll
+    for (int i = 0; i < 2; ++i) q[0][i] = *reinterpret_cast<const double2 *>(q0 + 4 * i);
+#pragma unroll
+    for (int b = 0; b < LC / 2; ++b) {
+        if (b + 1 < LC / 2)
+#pragma unroll
+            for (int i = 0; i < 2; ++i) q[(b + 1) & 1][i] = *reinterpret_cast<const double2 *>(q0 + 4 * (2 * b + 2 + i));
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            const int t = 2 * b + i;
+            const double2 qt = q[b & 1][i];
+            const bool skip = GEN && t == 0 && before;
+            out[chunk_row<LC, PSPLIT>(t) * stride] = GEN && (skip || c.k != 0) ? (T)0 : (T)c.mu;
+            if (skip) continue;
+            if (DIFF) {
+                const double eps = fma(qt.y, c.ms2, qt.x);
+                c.aux = fma(eps, c.mu, c.aux);
+                c.mu += c.aux;
+            } else {
+                const double nx = fma(fma(qt.x, c.x, qt.y), c.mu, -c.aux);
+                c.aux = c.mu;
+                c.mu = nx;
+            }
+            if (GEN) {
+                const bool up = c.k < 0 && fabs(c.mu) >= thr;
+                c.mu = up ? c.mu * down : c.mu;
+                c.aux = up ? c.aux * down : c.aux;
+                c.k += up ? 1 : 0;
+            }
+        }
+        __builtin_amdgcn_sched_barrier(0);
+    }
+}
+
 }  // namespace sht

@@ -42,49 +42,6 @@ struct SynSpinShared {
     int bad;                   // a coefficient of this item is Inf or NaN: no chunk is left out
 };
 
-// A chunk of the recursion into out[t LROW].  GEN: before (degree offset 0 lies below
-// l0: no output, no step) and lanes whose scale is below 0 (no output; rescaled).  The
-// coefficients of two steps are read together, one pair ahead of their use.
-template <bool DIFF, bool GEN, typename T>
-__device__ __forceinline__ void spin_chain_run(Chain &c, const double4 *cf, bool before, double thr, double down, T *out)
-{
-    const double *q0 = reinterpret_cast<const double *>(cf) + (DIFF ? 2 : 0);
-    double2 q[2][2];
-#pragma unroll
-    for (int i = 0; i < 2; ++i) q[0][i] = *reinterpret_cast<const double2 *>(q0 + 4 * i);
-#pragma unroll
-    for (int b = 0; b < SS_LC / 2; ++b) {
-        if (b + 1 < SS_LC / 2)
-#pragma unroll
-            for (int i = 0; i < 2; ++i) q[(b + 1) & 1][i] = *reinterpret_cast<const double2 *>(q0 + 4 * (2 * b + 2 + i));
-        __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-        for (int i = 0; i < 2; ++i) {
-            const int t = 2 * b + i;
-            const double2 qt = q[b & 1][i];
-            const bool skip = GEN && t == 0 && before;
-            out[t * SS_LROW] = GEN && (skip || c.k != 0) ? (T)0 : (T)c.mu;
-            if (skip) continue;
-            if (DIFF) {
-                const double eps = fma(qt.y, c.ms2, qt.x);
-                c.aux = fma(eps, c.mu, c.aux);
-                c.mu += c.aux;
-            } else {
-                const double nx = fma(fma(qt.x, c.x, qt.y), c.mu, -c.aux);
-                c.aux = c.mu;
-                c.mu = nx;
-            }
-            if (GEN) {
-                const bool up = c.k < 0 && fabs(c.mu) >= thr;
-                c.mu = up ? c.mu * down : c.mu;
-                c.aux = up ? c.aux * down : c.aux;
-                c.k += up ? 1 : 0;
-            }
-        }
-        __builtin_amdgcn_sched_barrier(0);
-    }
-}
-
 template <int NCB, bool F32, int NW>
 __device__ __forceinline__ void synth_spin_item(const LegView &v, const WaveItem it, const double *__restrict__ alm,
                                                 double *__restrict__ phase, int flush_chunks, int deriv,
@@ -185,14 +142,14 @@ __device__ __forceinline__ void synth_spin_item(const LegView &v, const WaveItem
             const bool before = lc < l0;
             bool now = live;
             if (slow || before) {
-                if (diff) spin_chain_run<true, true>(cs, cf, before, thr, down, lout);
-                else spin_chain_run<false, true>(cs, cf, before, thr, down, lout);
+                if (diff) chain_run<LC, false, true, true>(cs, cf, before, thr, down, lout, SS_LROW);
+                else chain_run<LC, false, false, true>(cs, cf, before, thr, down, lout, SS_LROW);
                 slow = wave_any(cs.k < 0);
                 now = wave_any(cs.k == 0 && (cs.mu != 0.0 || cs.aux != 0.0));
             } else if (diff) {
-                spin_chain_run<true, false>(cs, cf, false, thr, down, lout);
+                chain_run<LC, false, true, false>(cs, cf, false, thr, down, lout, SS_LROW);
             } else {
-                spin_chain_run<false, false>(cs, cf, false, thr, down, lout);
+                chain_run<LC, false, false, false>(cs, cf, false, thr, down, lout, SS_LROW);
             }
             now = now || sh.bad;
             __builtin_amdgcn_s_setprio(0);

@@ -186,9 +186,10 @@ constexpr double SPLIT_SIN = 0.2;
 // units) and a second chain of recursions over l in each direction; it pays from these
 // sizes on, whatever the spin and the direction.
 // Matrix cores, coefficients x slots; transform and inverse on Gauss-Legendre rings,
-// spin 2, spin kernels / scalar part, 4 and 16 transforms: lmax 800 (1.3e8)
-// 978 / 1028, 2879 / 2915 us; 1000 (2.5e8) 1552 / 1556, 4845 / 4437; 1200 (4.3e8)
-// 2198 / 1927, 6595 / 5410; batches of four such plans the same within 5%.
+// spin kernels / scalar part, us, 4 and 16 transforms: lmax 800 (1.3e8) 837 / 1028,
+// 2693 / 2915; 1000 (2.5e8) 1375 / 1556, 4540 / 4437; 1120 (3.5e8) 2451 / 2169, 8328 /
+// 7229; 1500 (8.5e8) 3695 / 2890, 11826 / 9330; batches of four such plans the same
+// within 5%.
 constexpr int64_t SPLIT_WORK = 330000000;
 // Vector units: where the spin kernels take two slots per lane, that is more than 64
 // slots (one spin-2 transform: lmax 120, 61 slots, 62 / 71 us; 128, 65 slots, 83 / 72).
