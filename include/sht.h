@@ -43,8 +43,8 @@
  *     stream-ordered work and must stay valid until that work completes;
  *   - geometry, plan and batch objects are owned by the library and freed by
  *     their destroy functions; a plan owns its device tables and its phase
- *     workspace (ntrans * ncomp * nrings * (mmax+1) * 16 bytes) and, for spins 1
- *     and 2 in FP64, of the coefficients' (degrees to lmax + spin);
+ *     workspace (ntrans * ncomp * nrings * (mmax+1) * 16 bytes), from some size on
+ *     with one more of the coefficients' size (spins 1 and 2 in FP64);
  *   - a plan (or batch) must not be executed on two streams at once.
  *
  * Errors

@@ -361,20 +361,30 @@ int slot_mlim(const PlanShape &ps, const SlotHost &s)
 }
 
 // Fills tables of `total` entries, every m a chain of its own: fill(k, n) does the
-// m = k, k + n, ...  Large tables by several threads.
+// m = k, k + n, ...  Large tables by several threads.  A failed allocation in any of
+// them is thrown here, after all have ended.
 template <typename Fill>
 static void fill_by_m(int64_t total, Fill fill)
 {
     const int nt = total < (1 << 18) ? 1 : (int)std::min(8u, std::max(1u, std::thread::hardware_concurrency()));
+    std::atomic<bool> failed{false};
+    auto run = [&](int k) {
+        try {
+            fill(k, nt);
+        } catch (const std::bad_alloc &) {
+            failed = true;
+        }
+    };
     std::vector<std::thread> others;
     others.reserve(nt);
     try {
-        for (int k = 1; k < nt; ++k) others.emplace_back(fill, k, nt);
+        for (int k = 1; k < nt; ++k) others.emplace_back(run, k);
     } catch (const std::system_error &) {   // fewer threads than asked for: the rest is done here
     }
-    fill(0, nt);
-    for (int k = (int)others.size() + 1; k < nt; ++k) fill(k, nt);
+    run(0);
+    for (int k = (int)others.size() + 1; k < nt; ++k) run(k);
     for (std::thread &t : others) t.join();
+    if (failed) throw std::bad_alloc();
 }
 
 // Per-m recursion coefficients for the rescaled recursion used on the GPU.
