@@ -173,14 +173,19 @@ int build_synth_items(Plan &p)
                       "upload");
 }
 
-// slots with sin t below this keep the spin kernels in a plan with a scalar part:
-// the division by sin^s t multiplies the rounding of the spin-0 sums there.
-// Relative rms error of spin-2 maps by ring against long double sums (C_l =
-// 1/(l + 1)^2, lmax 511; spin kernels / scalar part): sin t 0.05-0.1 2.4e-15 /
-// 2.2e-14, 0.1-0.2 1.7e-15 / 5.2e-15, 0.2-0.3 1.3e-15 / 2.1e-15, from 0.3 on equal
-// within 10%; over all rings 2.4e-15 in the spin kernels, and in a plan with the
-// line anywhere from 0.2 to 0.8.
-constexpr double SPLIT_SIN = 0.2;
+// Slots with sin t below this keep the spin kernels in a plan with a scalar part: the
+// division by sin^s t multiplies the rounding of the spin-0 sums, by about 0.7 / sin^2 t
+// units of the last place (spin 2), beside the recursion's own error, which grows with
+// lmax.  Relative rms error of phases, scalar part over spin kernels (C_l = 1/(l + 1)^2,
+// the larger of vector and matrix kernels, 80 rings in the band of 0.05 with the line):
+// spin 2, lmax 40 1.04, 80 1.09, 130 1.08, 200 1.07, 383 1.10, 1279 1.13; spin 1, 40 1.05,
+// 80 1.10, 130 1.05, 200 1.07.  At sin t = 0.20-0.25 instead: 3.3, 2.6, 2.6, 2.2, 1.5, 1.1;
+// spin 1, 1.9, 1.3, 1.2, 1.1.  From lmax 1700 on 0.2: the error is the recursion's there
+// down to that line, and nearer the poles the split saves little.
+static double split_sin(const Plan &p)
+{
+    return std::max(0.2, (p.spin == 1 ? 1.7 : 2.4) / std::cbrt((double)p.lmax));
+}
 
 // A scalar part costs four more launches on the matrix cores (two on the vector
 // units) and a second chain of recursions over l in each direction; it pays from these
@@ -196,15 +201,18 @@ constexpr int64_t SPLIT_WORK = 330000000;
 constexpr int SPLIT_SLOTS_VALU = 65;
 
 // Number of slots of the plan that keep the spin kernels: all of them, or (spin 1
-// and 2 in FP64, from the sizes above) whole 32-slot tiles from the pole.
+// and 2 in FP64, from the sizes above) the whole 32-slot tiles from the pole that hold
+// those below the line.  (Rounded up: a given grid may have any number of rings next to
+// a pole, where the factor has no bound.)
 static int split_slots(const Plan &p)
 {
     const int n = (int)p.slots.size();
     if (p.precision != SHT_FP64 || (p.spin != 1 && p.spin != 2)) return n;
     if (default_tuning(p).valu ? n < SPLIT_SLOTS_VALU : p.nalm * n < SPLIT_WORK) return n;
     int np = 0;
-    while (np < n && p.slots[np].sth < SPLIT_SIN) ++np;
-    np = std::max(32, (np + 15) / 32 * 32);
+    const double line = split_sin(p);
+    while (np < n && p.slots[np].sth < line) ++np;
+    np = std::max(32, (np + 31) / 32 * 32);
     return n - np >= 16 ? np : n;
 }
 
