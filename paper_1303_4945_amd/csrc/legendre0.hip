@@ -9,6 +9,10 @@
 //   cos^2 t > 1/2:  d_{l+2} = (t_l - 2) mu_l + d_l,  mu_{l+2} = mu_l + d_{l+2},
 //                   t_l - 2 = (a_l + b_l - 2) - a_l sin^2 t;
 //   else the same for (-1)^k mu (k the step), with -(t_l + 2) = -(b_l + 2) - a_l cos^2 t.
+// Each lane takes the form of its own slot: about the pole a colatitude is held to
+// 2^-54 tan t, which next to the equator has no bound.  (Wavefronts of one form by any
+// slot's cos^2 t > 1/2, GL rings at lmax 63, where one wavefront has them all: relative
+// error 2.0e-15 against 0.7e-15, 1.2e-14 at the ring next to the equator.)
 // Extended exponent as in the other kernels (a lane contributes while its scale
 // is 0); a chunk of degrees in which no lane of a wavefront has reached scale 0
 // takes no products (5% of the chunks at lmax 777, 12% at 4095).
@@ -40,20 +44,19 @@ __device__ __forceinline__ void for_each_of(F f)
 }
 
 struct Chain2 {
-    double w;    // -sin^2 t (pole form) or -cos^2 t (equator form)
-    double mu;   // mu_l
+    double w;    // sin^2 t (pole form) or -cos^2 t (equator form): the sign bit tells the form
+    double mu;   // mu_l (equator form: times (-1)^k)
     double d;    // difference
     int k;       // scale index (value = mu 2^(S k)), k <= 0
+    __device__ bool eq() const { return __double2hiint(w) < 0; }
 };
 
-// cos^2 t > 1/2 for any slot of the wavefront: pole form
-__device__ __forceinline__ Chain2 chain2_init(const LegView &v, int m, int slot, int par, double thr, double down,
-                                              bool &pole)
+__device__ __forceinline__ Chain2 chain2_init(const LegView &v, int m, int slot, int par, double thr, double down)
 {
     const Chain c = chain_init(v, m, slot, 0);
-    pole = wave_any(c.x * c.x > 0.5);
+    const bool eq = !(c.x * c.x > 0.5);
     Chain2 r;
-    r.w = slot < v.nslots ? -(pole ? v.slot_s2 : v.slot_c2)[slot] : 0.0;
+    r.w = slot < v.nslots ? (eq ? -v.slot_c2[slot] : v.slot_s2[slot]) : -0.0;
     r.k = c.k;
     // lambda_{m+1} = sqrt(2 m + 3) cos t lambda_m
     r.mu = par ? c.mu * (c.x * sqrt((double)(2 * m + 3))) : c.mu;
@@ -66,20 +69,17 @@ __device__ __forceinline__ Chain2 chain2_init(const LegView &v, int m, int slot,
 }
 
 // Step j of a chunk (an even number of steps, from an even step of the chain) with
-// the step coefficients q = (a, a + b - 2), or (-(b + 2), a) in the equator form:
-// returns mu_l (0 while the scale is below 0, SLOW) and moves on by two degrees.
-template <bool POLE, bool SLOW>
+// the step coefficients q of the lane's form: returns mu_l (0 while the scale is below
+// 0, SLOW) and moves on by two degrees.
+template <bool SLOW>
 __device__ __forceinline__ double chain2_step(Chain2 &c, const double2 q, int j, double thr, double down)
 {
-    const double eps = POLE ? fma(q.x, c.w, q.y) : fma(q.y, c.w, q.x);
-    const double out = SLOW ? (c.k == 0 ? c.mu : 0.0) : c.mu;
-    if (POLE || !(j & 1)) {
-        c.d = fma(eps, c.mu, c.d);
-        c.mu = POLE ? c.mu + c.d : -(c.mu + c.d);
-    } else {   // odd step of the equator form: mu holds (-1)^k times the chain
-        c.d = fma(-eps, c.mu, c.d);
-        c.mu = c.d - c.mu;
-    }
+    const double eps = fma(-q.x, fabs(c.w), q.y);
+    double out = SLOW ? (c.k == 0 ? c.mu : 0.0) : c.mu;
+    if (j & 1)   // (by integer instructions, which run beside matrix instructions)
+        out = __hiloint2double(__double2hiint(out) ^ (__double2hiint(c.w) & (int)0x80000000), __double2loint(out));
+    c.d = fma(eps, c.mu, c.d);
+    c.mu += c.d;
     if (SLOW) {
         const bool up = c.k < 0 && fabs(c.mu) >= thr;
         c.mu = up ? c.mu * down : c.mu;
@@ -89,15 +89,16 @@ __device__ __forceinline__ double chain2_step(Chain2 &c, const double2 q, int j,
     return out;
 }
 
-// NS steps (a chunk) into out[j stride]; cf: staged (a, a + b - 2, -(b + 2), a) of the
-// chunk's degrees, this class's at 2 j.  The coefficients of NB steps are read
-// together, one batch ahead of the steps that use them: read where they are used,
-// every step would wait for the LDS (130 cycles against the 24 of its arithmetic).
-template <int NS, int NB, bool POLE, bool SLOW>
+// NS steps (a chunk) into out[j stride]; cf: staged (a, a + b - 2, a, -(b + 2)) of the
+// chunk's degrees, this class's at 2 j, of which a lane reads its form's pair.  The
+// coefficients of NB steps are read together, one batch ahead of the steps that use
+// them: read where they are used, every step would wait for the LDS (130 cycles against
+// the 24 of its arithmetic).
+template <int NS, int NB, bool SLOW>
 __device__ __forceinline__ void chain2_run(Chain2 &c, const double4 *cf, double thr, double down, double *out,
                                            int stride)
 {
-    const double *q0 = reinterpret_cast<const double *>(cf) + (POLE ? 0 : 2);
+    const double *q0 = reinterpret_cast<const double *>(cf) + (c.eq() ? 2 : 0);
     double2 q[2][NB];
 #pragma unroll
     for (int i = 0; i < NB; ++i) q[0][i] = *reinterpret_cast<const double2 *>(q0 + 8 * i);
@@ -110,25 +111,19 @@ __device__ __forceinline__ void chain2_run(Chain2 &c, const double4 *cf, double 
 #pragma unroll
         for (int i = 0; i < NB; ++i) {
             const int j = b * NB + i;
-            out[j * stride] = chain2_step<POLE, SLOW>(c, q[b & 1][i], j, thr, down);
+            out[j * stride] = chain2_step<SLOW>(c, q[b & 1][i], j, thr, down);
         }
         __builtin_amdgcn_sched_barrier(0);
     }
 }
 
-// (the form and the masks by branches that every lane takes alike)
+// (the masks by a branch that every lane takes alike)
 template <int NS, int NB>
-__device__ __forceinline__ void chain2_chunk(Chain2 &c, bool pole, bool slow, const double4 *cf, double thr,
-                                             double down, double *out, int stride)
+__device__ __forceinline__ void chain2_chunk(Chain2 &c, bool slow, const double4 *cf, double thr, double down,
+                                             double *out, int stride)
 {
-    if (slow) {
-        if (pole) chain2_run<NS, NB, true, true>(c, cf, thr, down, out, stride);
-        else chain2_run<NS, NB, false, true>(c, cf, thr, down, out, stride);
-    } else if (pole) {
-        chain2_run<NS, NB, true, false>(c, cf, thr, down, out, stride);
-    } else {
-        chain2_run<NS, NB, false, false>(c, cf, thr, down, out, stride);
-    }
+    if (slow) chain2_run<NS, NB, true>(c, cf, thr, down, out, stride);
+    else chain2_run<NS, NB, false>(c, cf, thr, down, out, stride);
 }
 
 // After a chunk: whether any lane contributed (or may have); live: some lane's
@@ -140,7 +135,7 @@ __device__ __forceinline__ bool chain2_done(const Chain2 &c, bool live, bool &sl
     return wave_any(c.k == 0 && c.mu != 0.0);
 }
 
-__device__ __forceinline__ double4 chain2_coef(const double4 q) { return double4{q.x, q.y, q.z, q.x}; }
+__device__ __forceinline__ double4 chain2_coef(const double4 q) { return double4{q.x, q.y, q.x, q.z}; }
 
 // ---------------------------------------------------------------- synthesis
 //
@@ -185,8 +180,7 @@ __device__ __forceinline__ void synth0_item(const LegView &v, const WaveItem it,
     const int slot0 = it.tile * 64 + 32 * wave;
     const bool act = slot0 < v.nslots && v.tile_mlim[slot0 >> 6] >= m;
 
-    bool pole;
-    Chain2 cs = chain2_init(v, m, act ? slot0 + (lane & 31) : v.nslots, lane >> 5, thr, down, pole);
+    Chain2 cs = chain2_init(v, m, act ? slot0 + (lane & 31) : v.nslots, lane >> 5, thr, down);
     bool slow = wave_any(cs.k < 0);
     const bool live = wave_any(cs.mu != 0.0);
 
@@ -260,7 +254,7 @@ __device__ __forceinline__ void synth0_item(const LegView &v, const WaveItem it,
         if (more) fetch(lc + LC);
         if (act) {
             __builtin_amdgcn_s_setprio(2);
-            chain2_chunk<LC / 2, 2>(cs, pole, slow, &sh.cf[buf][lane >> 5], thr, down, lout, LSTEP);
+            chain2_chunk<LC / 2, 2>(cs, slow, &sh.cf[buf][lane >> 5], thr, down, lout, LSTEP);
             const bool now = chain2_done(cs, live, slow) || sh.bad;
             __builtin_amdgcn_s_setprio(0);
             wave_sync();
@@ -413,8 +407,7 @@ __device__ __forceinline__ void anal0_item(const LegView &v, const int m, const 
         };
         const int rtile = tile_at(wave >> 1);      // this wavefront's recursion region
         const bool ract = rtile >= 0;
-        bool pole;
-        Chain2 cs = chain2_init(v, m, ract ? rtile * 64 + 32 * (wave & 1) + rslot : v.nslots, rpar, thr, down, pole);
+        Chain2 cs = chain2_init(v, m, ract ? rtile * 64 + 32 * (wave & 1) + rslot : v.nslots, rpar, thr, down);
         bool slow = wave_any(cs.k < 0);
         const bool live = wave_any(cs.mu != 0.0);
 
@@ -503,7 +496,7 @@ __device__ __forceinline__ void anal0_item(const LegView &v, const int m, const 
             double prev[NR];
 #pragma unroll
             for (int r = 0; r < NR; ++r) prev[r] = !first && r < nout ? o[r * ostride] : 0.0;
-            if (ract) chain2_chunk<LC / 2, NCB == 4 ? 4 : 2>(cs, pole, slow, &sh.cf[rpar], thr, down, lout, LROW);
+            if (ract) chain2_chunk<LC / 2, NCB == 4 ? 4 : 2>(cs, slow, &sh.cf[rpar], thr, down, lout, LROW);
             const bool any = ract && chain2_done(cs, live, slow);
             if (lane == 0) sh.on[wave] = any ? 1 : 0;
             __syncthreads();
