@@ -132,7 +132,7 @@ __device__ __forceinline__ bool chain2_done(const Chain2 &c, bool live, bool &sl
 {
     if (!slow) return live;
     slow = wave_any(c.k < 0);
-    return wave_any(c.k == 0 && c.mu != 0.0);
+    return wave_any(c.k == 0 && (c.mu != 0.0 || c.d != 0.0));   // (mu can be 0 between two degrees that are not)
 }
 
 __device__ __forceinline__ double4 chain2_coef(const double4 q) { return double4{q.x, q.y, q.x, q.z}; }
