@@ -863,6 +863,19 @@ __device__ __forceinline__ void chain_step(Chain &c, const double4 q)
     }
 }
 
+// chain k of NCH per slot, the first ND slots in difference form
+template <int ND, int NCH>
+__device__ __forceinline__ void chains_step(Chain &c, int k, const double4 q)
+{
+    if (k / NCH < ND) {
+        if (NCH == 2 && (k & 1)) chain_step<true, true>(c, q);
+        else chain_step<true>(c, q);
+    } else {
+        if (NCH == 2 && (k & 1)) chain_step<false, true>(c, q);
+        else chain_step<false>(c, q);
+    }
+}
+
 // One chunk of LC degrees lc .. lc+LC-1 of the K chains of every lane, in
 // groups of G degrees: emit(u, k, mu, d) for each degree offset t = g + u and
 // chain k, with mu = mu_l (0 outside [l0, lmax] and while the chain's scale
@@ -871,7 +884,7 @@ __device__ __forceinline__ void chain_step(Chain &c, const double4 q)
 // degrees of a group are unrolled, so the caller's registers are indexed by u
 // alone and the compiler cannot keep the mu of the whole chunk alive.  The masked form
 // runs the groups below offset `last` only.
-template <int LC, int G, int K, bool DIFF, int NCH, typename Load, typename Emit, typename GroupEnd>
+template <int LC, int G, int K, int ND, int NCH, typename Load, typename Emit, typename GroupEnd>
 __device__ __forceinline__ void chains_chunk(Chain (&c)[K], bool &slow, int l0, int lc, int lmax, double thr,
                                              double down, int last, Load load, Emit emit, GroupEnd gend)
 {
@@ -887,8 +900,7 @@ __device__ __forceinline__ void chains_chunk(Chain (&c)[K], bool &slow, int l0, 
 #pragma unroll
                 for (int k = 0; k < K; ++k) {
                     emit(u, k, c[k].mu, d);
-                    if (NCH == 2 && (k & 1)) chain_step<DIFF, true>(c[k], d.q);
-                    else chain_step<DIFF>(c[k], d.q);
+                    chains_step<ND, NCH>(c[k], k, d.q);
                 }
             }
             gend(g);
@@ -913,8 +925,7 @@ __device__ __forceinline__ void chains_chunk(Chain (&c)[K], bool &slow, int l0, 
 #pragma unroll
                 for (int k = 0; k < K; ++k) {
                     emit(u, k, c[k].mu * on[k], d);
-                    if (NCH == 2 && (k & 1)) chain_step<DIFF, true>(c[k], d.q);
-                    else chain_step<DIFF>(c[k], d.q);
+                    chains_step<ND, NCH>(c[k], k, d.q);
                 }
             }
         } else {
@@ -926,10 +937,7 @@ __device__ __forceinline__ void chains_chunk(Chain (&c)[K], bool &slow, int l0, 
 #pragma unroll
                 for (int k = 0; k < K; ++k) {
                     emit(u, k, in ? c[k].mu * on[k] : 0.0, d);
-                    if (steps) {
-                        if (NCH == 2 && (k & 1)) chain_step<DIFF, true>(c[k], d.q);
-                        else chain_step<DIFF>(c[k], d.q);
-                    }
+                    if (steps) chains_step<ND, NCH>(c[k], k, d.q);
                 }
             }
         }
@@ -948,25 +956,45 @@ __device__ __forceinline__ void chains_chunk(Chain (&c)[K], bool &slow, int l0, 
     slow = wave_any(any);
 }
 
-// chains of the K slots of this lane (tile[k] < 0: none), the form (difference
-// form if any slot of the wave is close to a pole) and the scale flag
-template <int K, int NCH = 1>
+// Chains of the K slots of this lane (tile[k] < 0: none), the number of slots in
+// difference form (EACH: the first ones, up to the last 64 of the wavefront with one
+// close to a pole; otherwise all or none) and the scale flag.
+template <int K, int NCH, bool EACH>
 __device__ __forceinline__ void chains_init(const LegView &v, int m, const int (&tile)[K], int lane,
-                                            Chain (&c)[K * NCH], bool &diff, bool &slow)
+                                            Chain (&c)[K * NCH], int &ndiff, bool &slow)
 {
-    bool d = false, s = false;
+    ndiff = 0;
+    bool s = false;
 #pragma unroll
     for (int k = 0; k < K * NCH; ++k) {
         const int kt = k / NCH;
         c[k] = chain_init(v, m, tile[kt] >= 0 ? tile[kt] * 64 + lane : v.nslots, k % NCH);
-        d = d || c[k].x > DIFF_FORM_COS;
+        if (wave_any(c[k].x > DIFF_FORM_COS)) ndiff = EACH ? kt + 1 : K;
         s = s || c[k].k < 0;
     }
-    diff = wave_any(d);
     slow = wave_any(s);
-    if (diff)
 #pragma unroll
-        for (int k = 0; k < K * NCH; ++k) c[k].aux = c[k].mu;
+    for (int k = 0; k < K * NCH; ++k)
+        if (k / NCH < ndiff) c[k].aux = c[k].mu;
+}
+
+// run(number of slots in difference form, as a constant).  EACH, for the kernels of two
+// transforms that run the scalar parts: the form changes by 64 slots, not by the K 64 of a
+// wavefront, whose rings next to the equator the difference form holds less exactly (one
+// spin-2 transform at lmax 383 on given colatitudes: 1.26 of the spin kernels' error with
+// one form per wavefront, 0.99 so).  With one transform the third routine costs a
+// wavefront per SIMD (122 -> 132 registers).
+template <int K, bool EACH, typename Run>
+__device__ __forceinline__ void by_form(int ndiff, Run run)
+{
+    if (ndiff == 0) return run(std::integral_constant<int, 0>{});
+    if constexpr (EACH && K > 1)
+        if (ndiff == 1) return run(std::integral_constant<int, 1>{});
+    if constexpr (EACH && K > 2)
+        if (ndiff == 2) return run(std::integral_constant<int, 2>{});
+    if constexpr (EACH && K > 3)
+        if (ndiff == 3) return run(std::integral_constant<int, 3>{});
+    run(std::integral_constant<int, K>{});
 }
 
 // Degrees per chunk of the vector synthesis: 32, a chunk's recursion then covers more of
@@ -1000,8 +1028,9 @@ __device__ __forceinline__ void synth_valu_item(const LegView &v, const WaveItem
 #pragma unroll
     for (int k = 0; k < K; ++k) tile[k] = it.tile + k < v.ntiles ? it.tile + k : -1;
     Chain cs[K];
-    bool diff, slow;
-    chains_init<K>(v, m, tile, lane, cs, diff, slow);
+    int ndiff;
+    bool slow;
+    chains_init<K, 1, (J > 1)>(v, m, tile, lane, cs, ndiff, slow);
 
     // lane t < LC fetches degree lc + t of a chunk (clamped addresses; masked
     // when staged)
@@ -1045,13 +1074,13 @@ __device__ __forceinline__ void synth_valu_item(const LegView &v, const WaveItem
     stage(0, l0);
     wave_sync();
     auto run = [&](auto form) {
-        constexpr bool DIFF = decltype(form)::value;
+        constexpr int ND = decltype(form)::value;
         int chunk = 0;
         for (int lc = l0; lc <= lmax; lc += LC, ++chunk) {
             const int buf = chunk & 1;
             const bool more = lc + LC <= lmax;
             if (more) fetch(lc + LC);
-            chains_chunk<LC, 4, K, DIFF, 1>(
+            chains_chunk<LC, 4, K, ND, 1>(
                 cs, slow, l0, lc, lmax, thr, down, std::min(LC, lmax + 1 - lc),
                 [&](int t) -> const SynStage<J> & { return st[buf][t]; },
                 [&](int u, int k, double mu, const SynStage<J> &d) {
@@ -1067,8 +1096,7 @@ __device__ __forceinline__ void synth_valu_item(const LegView &v, const WaveItem
             wave_sync();
         }
     };
-    if (diff) run(std::true_type{});
-    else run(std::false_type{});
+    by_form<K, (J > 1)>(ndiff, run);
 
     // ring t = A0 + A1, ring pi - t = A0 - A1
     double2 *ph = reinterpret_cast<double2 *>(phase);
@@ -1140,8 +1168,9 @@ __device__ __forceinline__ void synth_valu_s_item(const LegView &v, const WaveIt
         tile[k] = u * 64 < v.nslots ? u : -1;
     }
     Chain cs[2 * K];   // chain 2k: +s of slot k, 2k + 1: -s
-    bool diff, slow;
-    chains_init<K, 2>(v, m, tile, lane, cs, diff, slow);
+    int ndiff;
+    bool slow;
+    chains_init<K, 2, false>(v, m, tile, lane, cs, ndiff, slow);
     const int ncin = deriv ? 1 : 2;   // input components per transform
 
     // lane t < LC fetches degree lc + t of a chunk (clamped addresses; masked when staged)
@@ -1189,13 +1218,13 @@ __device__ __forceinline__ void synth_valu_s_item(const LegView &v, const WaveIt
     wave_sync();
     double mu_p[K];   // the +s chain's value of the current degree (emitted before the -s chain)
     auto run = [&](auto form) {
-        constexpr bool DIFF = decltype(form)::value;
+        constexpr int ND = decltype(form)::value;
         int chunk = 0;
         for (int lc = lstart; lc <= lmax; lc += LC, ++chunk) {
             const int buf = chunk & 1;
             const bool more = lc + LC <= lmax;
             if (more) fetch(lc + LC);
-            chains_chunk<LC, 4, 2 * K, DIFF, 2>(
+            chains_chunk<LC, 4, 2 * K, ND, 2>(
                 cs, slow, l0, lc, lmax, thr, down, std::min(LC, lmax + 1 - lc),
                 [&](int t) -> const SynStageS<J> & { return st[buf][t]; },
                 [&](int u, int kc, double mu, const SynStageS<J> &d) {
@@ -1227,8 +1256,8 @@ __device__ __forceinline__ void synth_valu_s_item(const LegView &v, const WaveIt
             wave_sync();
         }
     };
-    if (diff) run(std::true_type{});
-    else run(std::false_type{});
+    if (ndiff) run(std::integral_constant<int, K>{});
+    else run(std::integral_constant<int, 0>{});
 
     // ring t = A0 + A1, ring pi - t = (-1)^s (A0 - A1); component 0: Q, 1: U
     double2 *ph = reinterpret_cast<double2 *>(phase);
@@ -1427,8 +1456,9 @@ __device__ __forceinline__ void anal_valu_item(const LegView &v, const int m, co
         }
         const bool active = tile[0] >= 0;   // tiles are dealt to k = 0 first
         Chain cs[K];
-        bool diff, slow;
-        chains_init<K>(v, m, tile, lane, cs, diff, slow);
+        int ndiff;
+        bool slow;
+        chains_init<K, 1, (J > 1)>(v, m, tile, lane, cs, ndiff, slow);
         // stationary phases G_t +- G_(pi-t) of the lane's slots (zero for missing
         // rings and slots, absent transforms)
         double2 g[K][2][J];
@@ -1509,8 +1539,9 @@ __device__ __forceinline__ void anal_valu_item(const LegView &v, const int m, co
                 for (int i = 0; i < 8; ++i) x[i] = 0.0;
             };
             if (active) {
-                if (diff) chains_chunk<LC, GD, K, true, 1>(cs, slow, l0, lc, lmax, thr, down, LC, load, emit, gend);
-                else chains_chunk<LC, GD, K, false, 1>(cs, slow, l0, lc, lmax, thr, down, LC, load, emit, gend);
+                by_form<K, (J > 1)>(ndiff, [&](auto form) {
+                    chains_chunk<LC, GD, K, decltype(form)::value, 1>(cs, slow, l0, lc, lmax, thr, down, LC, load, emit, gend);
+                });
             } else {
                 for (int e = lane; e < NV * 8; e += 64) part[buf][wave][e] = 0.0;
             }
@@ -1638,8 +1669,9 @@ __device__ __forceinline__ void anal_valu_s_item(const LegView &v, const int m, 
         }
         const bool active = tile[0] >= 0;
         Chain cs[2 * K];
-        bool diff, slow;
-        chains_init<K, 2>(v, m, tile, lane, cs, diff, slow);
+        int ndiff;
+        bool slow;
+        chains_init<K, 2, false>(v, m, tile, lane, cs, ndiff, slow);
         // stationary phases (Q_re, Q_im, U_re, U_im) of the lane's slots per class
         double4 g[K][2][J];
 #pragma unroll
@@ -1728,8 +1760,8 @@ __device__ __forceinline__ void anal_valu_s_item(const LegView &v, const int m, 
                 for (int i = 0; i < 8; ++i) x[i] = 0.0;
             };
             if (active) {
-                if (diff) chains_chunk<LC, GD, 2 * K, true, 2>(cs, slow, l0, lc, lmax, thr, down, LC, load, emit, gend);
-                else chains_chunk<LC, GD, 2 * K, false, 2>(cs, slow, l0, lc, lmax, thr, down, LC, load, emit, gend);
+                if (ndiff) chains_chunk<LC, GD, 2 * K, K, 2>(cs, slow, l0, lc, lmax, thr, down, LC, load, emit, gend);
+                else chains_chunk<LC, GD, 2 * K, 0, 2>(cs, slow, l0, lc, lmax, thr, down, LC, load, emit, gend);
             } else {
                 for (int e = lane; e < NV * 8; e += 64) part[buf][wave][e] = 0.0;
             }
