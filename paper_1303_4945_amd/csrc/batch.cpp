@@ -8,6 +8,7 @@
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
+#include <memory>
 #include <new>
 #include <string>
 #include <vector>
@@ -137,20 +138,26 @@ void synth_queue(Batch &b, std::vector<BatchSynItem> &q)
     b.syn_ofs[NUM_XCD] = (int)q.size();
 }
 
+// No queue: the plans' own launches run until a later call builds it.
+void drop_synth_queue(Batch &b)
+{
+    dev_free(b.d_syn);
+    b.d_syn = nullptr;
+    b.nsyn = 0;
+    for (int &o : b.syn_ofs) o = 0;
+    b.syn_ok = false;
+    b.syn_gen.clear();
+}
+
 // (Re)builds the synthesis queue when the plans' work lists changed since it
 // was built, or when forced (new queue order).  Host work, a device
 // synchronization (the old queue may still be read) and an upload: refused
 // while the stream s is being captured.
 int refresh_synth_queue(Batch &b, hipStream_t s, bool force)
-{
+try {
     if (b.concurrent != 2) {   // only schedule 2 uses the queue: built when it is chosen
         if (b.d_syn) (void)hipDeviceSynchronize();
-        dev_free(b.d_syn);
-        b.d_syn = nullptr;
-        b.nsyn = 0;
-        for (int &o : b.syn_ofs) o = 0;
-        b.syn_ok = false;
-        b.syn_gen.clear();
+        drop_synth_queue(b);
         return SHT_OK;
     }
     std::vector<uint64_t> gen;
@@ -186,32 +193,38 @@ int refresh_synth_queue(Batch &b, hipStream_t s, bool force)
     synth_queue(b, q);
     int rc = dev_alloc((void **)&b.d_syn, std::max<size_t>(1, q.size()) * sizeof(BatchSynItem), "batch tables");
     if (!rc && !q.empty()) rc = dev_upload(b.d_syn, q.data(), q.size() * sizeof(BatchSynItem), "batch tables");
-    if (rc) {   // no queue: the plans' own launches run until a later call builds it
-        dev_free(b.d_syn);
-        b.d_syn = nullptr;
-        for (int &o : b.syn_ofs) o = 0;
-        b.syn_ok = false;
+    if (rc) {
+        drop_synth_queue(b);
         return rc;
     }
     b.nsyn = (int)q.size();
     b.syn_gen = gen;
     return SHT_OK;
+} catch (const std::bad_alloc &) {
+    drop_synth_queue(b);
+    return no_memory();
 }
 
 bool persistent_synth(const Batch &b) { return b.concurrent == 2 && b.syn_ok; }
 
+// (a failure leaves the queue as it was)
 int upload_queue(Batch &b)
-{
+try {
     std::vector<BatchAnaItem> aq;
     anal_queue(b, aq);
-    b.nana = (int)aq.size();
-    dev_free(b.d_ana);
-    b.d_ana = nullptr;
-    int rc;
-    if ((rc = dev_alloc((void **)&b.d_ana, std::max<size_t>(1, aq.size()) * sizeof(BatchAnaItem), "batch tables")))
+    BatchAnaItem *d = nullptr;
+    int rc = dev_alloc((void **)&d, std::max<size_t>(1, aq.size()) * sizeof(BatchAnaItem), "batch tables");
+    if (!rc && !aq.empty()) rc = dev_upload(d, aq.data(), aq.size() * sizeof(BatchAnaItem), "batch tables");
+    if (rc) {
+        dev_free(d);
         return rc;
-    if (!aq.empty()) return dev_upload(b.d_ana, aq.data(), aq.size() * sizeof(BatchAnaItem), "batch tables");
+    }
+    dev_free(b.d_ana);
+    b.d_ana = d;
+    b.nana = (int)aq.size();
     return SHT_OK;
+} catch (const std::bad_alloc &) {
+    return no_memory();
 }
 
 // Stream of plan i's launch chain: its own stream when the batch runs plans
@@ -308,7 +321,7 @@ int batch_legendre_synth(Batch &b, int direction, const double *const *in, doubl
 
 // Everything one execution of the batch puts on the stream.
 int batch_enqueue(Batch &b, int direction, const double *const *in, double *const *out, hipStream_t s)
-{
+try {
     const int np = (int)b.plans.size();
     int rc;
     if (synth_direction(direction) && persistent_synth(b)) {
@@ -347,6 +360,8 @@ int batch_enqueue(Batch &b, int direction, const double *const *in, double *cons
     std::vector<const double *> ph(np);
     for (int i = 0; i < np; ++i) ph[i] = b.plans[i]->d_phase;
     return batch_legendre_anal(b, direction, ph.data(), out, s);
+} catch (const std::bad_alloc &) {
+    return no_memory();
 }
 
 int check_batch_args(Batch *b, int direction, const double *const *in, double *const *out, bool leg_only)
@@ -452,7 +467,7 @@ void tune_cache_store(const std::string &key, const sht_tuning &t)
 extern "C" {
 
 int sht_batch_create(int nplans, sht_plan *const *plans, sht_batch **out)
-{
+try {
     TraceRange tr("sht_batch_create");
     if (!out) { set_error("out is NULL"); return SHT_EINVAL; }
     *out = nullptr;
@@ -461,25 +476,29 @@ int sht_batch_create(int nplans, sht_plan *const *plans, sht_batch **out)
         set_error("a batch holds at most %d plans", MAX_BATCH_PLANS);
         return SHT_EINVAL;
     }
-    Batch *b = new (std::nothrow) Batch();
-    if (!b) { set_error("host allocation failed"); return SHT_ENOMEM; }
+    struct Freed {   // (its device buffers, streams and events with it)
+        void operator()(Batch *x) const
+        {
+            batch_free(x);
+            delete x;
+        }
+    };
+    std::unique_ptr<Batch, Freed> owner(new Batch());
+    Batch *b = owner.get();
     int maxj = 0;
     for (int i = 0; i < nplans; ++i) {
         Plan *p = plan_of(plans[i]);
         if (!p) {
-            delete b;
             set_error("plan %d is not a valid plan", i);
             return SHT_ESTATE;
         }
         if (i > 0 && (p->spin != b->spin || p->precision != b->precision || p->device != b->plans[0]->device ||
                       p->real_h != b->real_h)) {
-            delete b;
             set_error("all plans of a batch must have the same spin, precision, device and coefficient storage");
             return SHT_EINVAL;
         }
         for (Plan *q : b->plans)
             if (q == p) {
-                delete b;
                 set_error("plan %d appears twice (plans share no workspace within a batch)", i);
                 return SHT_EINVAL;
             }
@@ -498,10 +517,7 @@ int sht_batch_create(int nplans, sht_plan *const *plans, sht_batch **out)
     // on the vector path now and retuned later)
     for (Plan *p : b->plans) {
         const int rc = two_step(*p) ? ensure_tables(*p, false) : SHT_OK;
-        if (rc) {
-            delete b;
-            return rc;
-        }
+        if (rc) return rc;
     }
     std::vector<LegView> views;
     for (Plan *p : b->plans) views.push_back(make_leg_view(*p));
@@ -509,11 +525,8 @@ int sht_batch_create(int nplans, sht_plan *const *plans, sht_batch **out)
     if ((rc = dev_alloc((void **)&b->d_views, views.size() * sizeof(LegView), "batch tables")) ||
         (rc = dev_upload(b->d_views, views.data(), views.size() * sizeof(LegView), "batch tables")) ||
         (rc = upload_queue(*b)) || (rc = refresh_synth_queue(*b, nullptr, true)) ||
-        (rc = dev_alloc((void **)&b->d_counter, 64 * (NUM_XCD + 2), "batch counters"))) {
-        batch_free(b);
-        delete b;
+        (rc = dev_alloc((void **)&b->d_counter, 64 * (NUM_XCD + 2), "batch counters")))
         return rc;
-    }
     for (int i = 0; i <= nplans && !rc; ++i) {
         hipEvent_t e = nullptr;
         rc = check_hip(hipEventCreateWithFlags(&e, hipEventDisableTiming), "batch events");
@@ -524,17 +537,15 @@ int sht_batch_create(int nplans, sht_plan *const *plans, sht_batch **out)
             if (!rc) b->aux.push_back(st);
         }
     }
-    if (rc) {
-        batch_free(b);
-        delete b;
-        return rc;
-    }
+    if (rc) return rc;
     const uint64_t serial = reg_add(b, H_BATCH);
     log_msg(1, "batch %llu created: %d plans, spin %d, %s, %d analysis queue items, %d persistent work groups",
             (unsigned long long)serial, nplans, b->spin, b->precision == SHT_FP64 ? "fp64" : "fp32_mfma", b->nana,
             b->ana_groups);
-    *out = reinterpret_cast<sht_batch *>(b);
+    *out = reinterpret_cast<sht_batch *>(owner.release());
     return SHT_OK;
+} catch (const std::bad_alloc &) {
+    return no_memory();
 }
 
 int sht_batch_configure(sht_batch *h, int queue_order, int concurrent)
@@ -603,7 +614,7 @@ int sht_batch_legendre(sht_batch *h, int direction, const double *const *in, dou
 
 int sht_batch_execute(sht_batch *h, int direction, const double *const *in, double *const *out,
                       void *hip_stream)
-{
+try {
     TraceRange tr("sht_batch_execute");
     if (!reg_live(h, H_BATCH)) { set_error("invalid batch handle"); return SHT_ESTATE; }
     Batch *b = reinterpret_cast<Batch *>(h);
@@ -649,6 +660,8 @@ int sht_batch_execute(sht_batch *h, int direction, const double *const *in, doub
         b->graph_stream[direction] = s;
     }
     return check_hip(hipGraphLaunch(b->graph[direction], s), "graph launch");
+} catch (const std::bad_alloc &) {
+    return no_memory();
 }
 
 void sht_batch_destroy(sht_batch *h)
@@ -663,7 +676,7 @@ void sht_batch_destroy(sht_batch *h)
 }
 
 int sht_autotune(sht_plan *h, double budget_seconds)
-{
+try {
     TraceRange tr("sht_autotune");
     Plan *p = plan_of(h);
     if (!p) { set_error("invalid plan handle"); return SHT_ESTATE; }
@@ -686,6 +699,8 @@ int sht_autotune(sht_plan *h, double budget_seconds)
         a_ncb.push_back(2);
     }
     const std::vector<int> s_mb = {2, 4, 8};
+    // (no host allocation between here and the end of the scratch that throws: the
+    // calls catch theirs)
     // scratch operands: zero coefficients and phases (the kernels' time does
     // not depend on the values)
     double *alm = nullptr;
@@ -755,6 +770,8 @@ int sht_autotune(sht_plan *h, double budget_seconds)
     tune_cache_store(key, best);
     log_msg(1, "plan %llu: autotuned %s", (unsigned long long)p->serial, tune_text(best).c_str());
     return SHT_OK;
+} catch (const std::bad_alloc &) {
+    return no_memory();
 }
 
 }  // extern "C"

@@ -13,6 +13,7 @@
 #include <cstdlib>
 #include <cstring>
 #include <mutex>
+#include <memory>
 #include <new>
 #include <system_error>
 #include <thread>
@@ -30,6 +31,12 @@ void set_error(const char *fmt, ...)
     vsnprintf(g_err, sizeof(g_err), fmt, ap);
     va_end(ap);
     if (g_err[0]) log_msg(1, "error: %s", g_err);
+}
+
+int no_memory()
+{
+    set_error("host allocation failed");
+    return SHT_ENOMEM;
 }
 
 int log_level()
@@ -154,11 +161,10 @@ static int validate_rings(int nrings, const double *theta, const int64_t *nphi,
     return SHT_OK;
 }
 
-static Geom *geom_from(int nrings, const double *theta, const int64_t *nphi, const double *phi0,
+static std::unique_ptr<Geom> geom_from(int nrings, const double *theta, const int64_t *nphi, const double *phi0,
                        const double *weight, const int64_t *ofs, int64_t stride)
 {
-    Geom *g = new (std::nothrow) Geom();
-    if (!g) return nullptr;
+    std::unique_ptr<Geom> g(new Geom());
     g->nrings = nrings;
     g->theta.assign(theta, theta + nrings);
     g->nphi.assign(nphi, nphi + nrings);
@@ -181,18 +187,6 @@ static Geom *geom_from(int nrings, const double *theta, const int64_t *nphi, con
 }
 
 static const long double PI_L = 3.14159265358979323846264338327950288L;
-
-// What the double colatitudes of a grid leave of the exact ones, ring by ring
-// (theta itself stays as given out).  A colatitude rounded to double moves the
-// phase of degree l by up to l 2^-53, as much as the recursion's own rounding.
-static int with_residual(int rc, const std::vector<long double> &exact, sht_geom **out)
-{
-    if (rc) return rc;
-    Geom *g = reinterpret_cast<Geom *>(*out);
-    g->theta_lo.resize(g->nrings);
-    for (int i = 0; i < g->nrings; ++i) g->theta_lo[i] = (double)(exact[i] - g->theta[i]);
-    return rc;
-}
 
 // Gauss-Legendre nodes as colatitudes by Newton's method on P_n(cos t) in
 // long double, with weights 2 / ((1 - x^2) P_n'(x)^2).
@@ -380,6 +374,7 @@ static void fill_by_m(int64_t total, Fill fill)
     try {
         for (int k = 1; k < nt; ++k) others.emplace_back(run, k);
     } catch (const std::system_error &) {   // fewer threads than asked for: the rest is done here
+    } catch (const std::bad_alloc &) {
     }
     run(0);
     for (int k = (int)others.size() + 1; k < nt; ++k) run(k);
@@ -633,6 +628,32 @@ namespace sht {
 const Geom *geom_of(const sht_geom *g) { return as_geom(g); }
 }  // namespace sht
 
+static int geom_out(std::unique_ptr<Geom> g, sht_geom **out)
+{
+    const uint64_t serial = reg_add(g.get(), H_GEOM);
+    log_msg(1, "geometry %llu created: %d rings, %lld pixels, %s", (unsigned long long)serial, g->nrings,
+            (long long)g->npix, g->has_weight ? "ring weights" : "no ring weights");
+    *out = reinterpret_cast<sht_geom *>(g.release());
+    return SHT_OK;
+}
+
+// A grid of the library, with what its double colatitudes leave of the exact ones, ring
+// by ring (theta itself stays as given out).  A colatitude rounded to double moves the
+// phase of degree l by up to l 2^-53, as much as the recursion's own rounding.
+static int library_grid(int nrings, const std::vector<double> &theta, const std::vector<int64_t> &nphi,
+                        const std::vector<double> &phi0, const std::vector<double> &weight,
+                        const std::vector<long double> &exact, sht_geom **out)
+{
+    const int rc = validate_rings(nrings, theta.data(), nphi.data(), phi0.data(), 1);
+    if (rc) return rc;
+    for (int i = 0; i < nrings; ++i)
+        if (!std::isfinite(weight[i])) { set_error("weight[%d] not finite", i); return SHT_EINVAL; }
+    std::unique_ptr<Geom> g = geom_from(nrings, theta.data(), nphi.data(), phi0.data(), weight.data(), nullptr, 1);
+    g->theta_lo.resize(nrings);
+    for (int i = 0; i < nrings; ++i) g->theta_lo[i] = (double)(exact[i] - theta[i]);
+    return geom_out(std::move(g), out);
+}
+
 extern "C" {
 
 const char *sht_last_error(void) { return g_err; }
@@ -669,7 +690,7 @@ int sht_memory_stats(int64_t *live_buffers, int64_t *live_bytes)
 
 int sht_geom_create(int nrings, const double *theta, const int64_t *nphi, const double *phi0,
                     const double *weight, const int64_t *ofs, int64_t stride, sht_geom **out)
-{
+try {
     if (!out) { set_error("out is NULL"); return SHT_EINVAL; }
     *out = nullptr;
     int rc = validate_rings(nrings, theta, nphi, phi0, stride);
@@ -680,17 +701,13 @@ int sht_geom_create(int nrings, const double *theta, const int64_t *nphi, const 
     if (weight)
         for (int i = 0; i < nrings; ++i)
             if (!std::isfinite(weight[i])) { set_error("weight[%d] not finite", i); return SHT_EINVAL; }
-    Geom *g = geom_from(nrings, theta, nphi, phi0, weight, ofs, stride);
-    if (!g) { set_error("host allocation failed"); return SHT_ENOMEM; }
-    const uint64_t serial = reg_add(g, H_GEOM);
-    log_msg(1, "geometry %llu created: %d rings, %lld pixels, %s", (unsigned long long)serial, g->nrings,
-            (long long)g->npix, g->has_weight ? "ring weights" : "no ring weights");
-    *out = reinterpret_cast<sht_geom *>(g);
-    return SHT_OK;
+    return geom_out(geom_from(nrings, theta, nphi, phi0, weight, ofs, stride), out);
+} catch (const std::bad_alloc &) {
+    return no_memory();
 }
 
 int sht_geom_gauss(int nrings, int64_t nphi, double phi0, sht_geom **out)
-{
+try {
     if (!out) { set_error("out is NULL"); return SHT_EINVAL; }
     *out = nullptr;
     if (nrings < 1 || nrings > 65536) { set_error("nrings %d outside [1, 65536]", nrings); return SHT_EINVAL; }
@@ -701,11 +718,13 @@ int sht_geom_gauss(int nrings, int64_t nphi, double phi0, sht_geom **out)
     std::vector<int64_t> np(nrings, nphi);
     std::vector<double> p0(nrings, phi0), wt(nrings);
     for (int i = 0; i < nrings; ++i) wt[i] = w[i] * (2.0 * M_PI / (double)nphi);
-    return with_residual(sht_geom_create(nrings, th.data(), np.data(), p0.data(), wt.data(), nullptr, 1, out), exact, out);
+    return library_grid(nrings, th, np, p0, wt, exact, out);
+} catch (const std::bad_alloc &) {
+    return no_memory();
 }
 
 int sht_geom_ecp(int nrings, int64_t nphi, int kind, double phi0, sht_geom **out)
-{
+try {
     if (!out) { set_error("out is NULL"); return SHT_EINVAL; }
     *out = nullptr;
     if (kind != SHT_ECP_FEJER1 && kind != SHT_ECP_FEJER2 && kind != SHT_ECP_CC) {
@@ -721,12 +740,14 @@ int sht_geom_ecp(int nrings, int64_t nphi, int kind, double phi0, sht_geom **out
     std::vector<int64_t> np(nrings, nphi);
     std::vector<double> p0(nrings, phi0), wt(nrings);
     for (int i = 0; i < nrings; ++i) wt[i] = w[i] * (2.0 * M_PI / (double)nphi);
-    return with_residual(sht_geom_create(nrings, th.data(), np.data(), p0.data(), wt.data(), nullptr, 1, out), exact, out);
+    return library_grid(nrings, th, np, p0, wt, exact, out);
+} catch (const std::bad_alloc &) {
+    return no_memory();
 }
 
 int sht_geom_reduced_gauss(int nrings, int64_t nphi_max, int lmax, int mmax, int spin, double phi0,
                            sht_geom **out)
-{
+try {
     if (!out) { set_error("out is NULL"); return SHT_EINVAL; }
     *out = nullptr;
     if (nrings < 1 || nrings > 65536) { set_error("nrings %d outside [1, 65536]", nrings); return SHT_EINVAL; }
@@ -751,11 +772,13 @@ int sht_geom_reduced_gauss(int nrings, int64_t nphi_max, int lmax, int mmax, int
         np[i] = std::min(n, nphi_max);
         wt[i] = w[i] * (2.0 * M_PI / (double)np[i]);
     }
-    return with_residual(sht_geom_create(nrings, th.data(), np.data(), p0.data(), wt.data(), nullptr, 1, out), exact, out);
+    return library_grid(nrings, th, np, p0, wt, exact, out);
+} catch (const std::bad_alloc &) {
+    return no_memory();
 }
 
 int sht_geom_healpix(int nside, sht_geom **out)
-{
+try {
     if (!out) { set_error("out is NULL"); return SHT_EINVAL; }
     *out = nullptr;
     if (nside < 1 || nside > 8192) { set_error("nside %d outside [1, 8192]", nside); return SHT_EINVAL; }
@@ -788,7 +811,9 @@ int sht_geom_healpix(int nside, sht_geom **out)
     th[2 * nside - 1] = 0.5 * M_PI;
     double npix = 12.0 * nside * (double)nside;
     for (int y = 0; y < nr; ++y) wt[y] = 4.0 * M_PI / npix;
-    return with_residual(sht_geom_create(nr, th.data(), np.data(), p0.data(), wt.data(), nullptr, 1, out), exact, out);
+    return library_grid(nr, th, np, p0, wt, exact, out);
+} catch (const std::bad_alloc &) {
+    return no_memory();
 }
 
 int sht_geom_info(const sht_geom *g, int *nrings, int64_t *npix)

@@ -14,6 +14,7 @@
 namespace sht {
 
 void set_error(const char *fmt, ...);
+int no_memory();   // SHT_ENOMEM with its message: what an entry point makes of std::bad_alloc
 
 // Diagnostics on stderr, one line each, by the level in $SHT_LOG (read once):
 // 0 off (default), 1 handles created and destroyed, tuning choices and errors,

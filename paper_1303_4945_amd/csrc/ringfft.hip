@@ -1471,6 +1471,7 @@ int fft_plan_build(Plan &p)
     // groups by LDS class
     std::map<std::tuple<int, int, int>, int> gid;
     FftDev *D = new FftDev();
+    p.fft.d_rows = D;
     for (int i = 0; i < (int)H.rows.size(); ++i) {
         const FftLen &d = H.lens[H.rows[i].len];
         int c = 256;
@@ -1491,7 +1492,6 @@ int fft_plan_build(Plan &p)
         if (gr.mode != KMODE_LDS && FFT_NREG * threads_for(gr) < gr.lds_complex) {
             set_error("FFT of %d complex points exceeds the register slots of its work group",
                       gr.lds_complex);
-            delete D;
             return SHT_EUNSUPPORTED;
         }
     int rc;
@@ -1508,21 +1508,15 @@ int fft_plan_build(Plan &p)
         (rc = up((void **)&D->ofs, g.ofs.data(), g.ofs.size() * sizeof(int64_t), "fft tables")) ||
         (rc = up((void **)&D->weight, g.weight.data(), g.weight.size() * sizeof(double), "fft tables")) ||
         (rc = up((void **)&D->rot, rot.data(), rot.size() * sizeof(double2), "fft tables")) ||
-        (rc = up((void **)&D->mvalid, mvalid.data(), mvalid.size() * sizeof(int), "fft tables"))) {
-        p.fft.d_rows = D;
+        (rc = up((void **)&D->mvalid, mvalid.data(), mvalid.size() * sizeof(int), "fft tables")))
         return rc;
-    }
     D->nrot = nrot;
     D->rot_trivial = std::all_of(g.phi0.begin(), g.phi0.end(), [](double x) { return x == 0.0; }) ? 1 : 0;
-    for (auto &gr : D->groups) {
-        int *dr = nullptr;
-        if ((rc = up((void **)&dr, gr.rows.data(), gr.rows.size() * sizeof(int), "fft rows"))) {
-            p.fft.d_rows = D;
-            return rc;
-        }
-        D->group_rows.push_back(dr);
+    D->group_rows.assign(D->groups.size(), nullptr);
+    for (size_t i = 0; i < D->groups.size(); ++i) {
+        const std::vector<int> &r = D->groups[i].rows;
+        if ((rc = up((void **)&D->group_rows[i], r.data(), r.size() * sizeof(int), "fft rows"))) return rc;
     }
-    p.fft.d_rows = D;
     p.fft.nrows = (int)H.rows.size();
     p.fft.table_bytes = H.ctab.size() * sizeof(double2) + H.itab.size() * sizeof(int);
     if ((rc = prepare_groups(*D))) return rc;

@@ -125,7 +125,14 @@ static void count_work(Plan &p)
 // i runs on die i mod NUM_XCD), so that the a_lm of an m and the cache lines
 // of its phases stay in one L2; blocks are dealt to the dies greedily by
 // cost, and each die's list runs from the longest degree range down.
-int build_synth_items(Plan &p)
+// the list of the plan's tuning, in host and device memory (empty: none there)
+struct SynthItems {
+    std::vector<WaveItem> host;
+    WaveItem *dev = nullptr;
+    ~SynthItems() { dev_free(dev); }
+};
+
+static int make_synth_items(const Plan &p, SynthItems &out)
 {
     const int cpj = p.spin ? 4 : 2;
     const int jpg = p.tune.valu ? valu_jpg(p) : p.tune.synth_ncb * 16 / cpj;
@@ -158,19 +165,29 @@ int build_synth_items(Plan &p)
     }
     size_t longest = 0;
     for (auto &l : die) longest = std::max(longest, l.size());
-    p.synth_items.assign(longest * NUM_XCD, WaveItem{-1, 0, 0, 0});
+    out.host.assign(longest * NUM_XCD, WaveItem{-1, 0, 0, 0});
     for (int d = 0; d < NUM_XCD; ++d)
-        for (size_t i = 0; i < die[d].size(); ++i) p.synth_items[i * NUM_XCD + d] = die[d][i];
+        for (size_t i = 0; i < die[d].size(); ++i) out.host[i * NUM_XCD + d] = die[d][i];
+    if (out.host.empty()) return SHT_OK;
+    const int rc = dev_alloc((void **)&out.dev, out.host.size() * sizeof(WaveItem), "item list");
+    return rc ? rc : dev_upload(out.dev, out.host.data(), out.host.size() * sizeof(WaveItem), "upload");
+}
+
+// makes it the plan's (the old one goes with it)
+static void take_synth_items(Plan &p, SynthItems &it)
+{
+    p.synth_items.swap(it.host);
+    std::swap(p.d_synth_items, it.dev);
     p.n_items = (int64_t)p.synth_items.size();
     ++p.generation;
-    dev_free(p.d_synth_items);
-    p.d_synth_items = nullptr;
-    if (p.synth_items.empty()) return SHT_OK;
-    int rc;
-    if ((rc = dev_alloc((void **)&p.d_synth_items, p.synth_items.size() * sizeof(WaveItem), "item list")))
-        return rc;
-    return dev_upload(p.d_synth_items, p.synth_items.data(), p.synth_items.size() * sizeof(WaveItem),
-                      "upload");
+}
+
+static int build_synth_items(Plan &p)
+{
+    SynthItems it;
+    const int rc = make_synth_items(p, it);
+    if (!rc) take_synth_items(p, it);
+    return rc;
 }
 
 // Slots with sin t below this keep the spin kernels in a plan with a scalar part: the
@@ -217,7 +234,7 @@ static int split_slots(const Plan &p)
 }
 
 int ensure_tables(Plan &p, bool valu)
-{
+try {
     const bool two = two_step(p) && !valu;
     if (two ? p.d_coef2 != nullptr : p.d_coef != nullptr) return SHT_OK;
     // the m that have an active slot
@@ -256,6 +273,8 @@ int ensure_tables(Plan &p, bool valu)
         p.d_fl = f;
     }
     return SHT_OK;
+} catch (const std::bad_alloc &) {   // (of a host table: nothing is on the device yet)
+    return no_memory();
 }
 
 // Tables of the Legendre kernels over the slots [first, first + p.nslots) of
@@ -347,8 +366,9 @@ static int anal_list_build(Plan &p, int top)
     return dev_upload(p.d_anal_ms, p.anal_ms.data(), p.anal_ms.size() * sizeof(int), "upload");
 }
 
+// (what it leaves behind when it fails is freed by the caller)
 static int plan_build(Plan &p, bool split)
-{
+try {
     int rc;
     // (the FP32 form rounds lambda to single precision: its results stay tied to the
     // colatitudes as given out)
@@ -358,8 +378,7 @@ static int plan_build(Plan &p, bool split)
     p.crit_spin = p.spin;
     p.crit_lmax = p.lmax;
     if (p.nslots < nall) {
-        p.eq.reset(new (std::nothrow) Plan());
-        if (!p.eq) { set_error("host allocation failed"); return SHT_ENOMEM; }
+        p.eq.reset(new Plan());
         Plan &e = *p.eq;
         e.device = p.device;
         e.lmax = p.lmax + p.spin; e.mmax = p.mmax; e.spin = 0; e.ntrans = p.ncomp * p.ntrans;
@@ -389,6 +408,8 @@ static int plan_build(Plan &p, bool split)
     if ((rc = fft_plan_build(p))) return rc;
     count_work(p);
     return SHT_OK;
+} catch (const std::bad_alloc &) {
+    return no_memory();
 }
 
 int slot_phase_mlim(const Plan &p, int slot)
@@ -439,28 +460,36 @@ int tuning_check(const Plan &p, const sht_tuning &t)
     return SHT_OK;
 }
 
+// The scalar part follows the choice of vector or matrix kernels and the m blocks; its
+// column blocks are its own.  A failure leaves the plan as it was: kernels, tables and
+// work lists belong together.
 int apply_tuning(Plan &p, const sht_tuning &t)
 {
     int rc = tuning_check(p, t);
     if (rc) return rc;
-    const sht_tuning old = p.tune;
-    // the scalar part follows the choice of vector or matrix kernels and the m
-    // blocks; its column blocks are its own
-    auto apply = [&](const sht_tuning &c) {
-        int r = ensure_tables(p, c.valu);
-        if (!r && p.eq) r = ensure_tables(*p.eq, c.valu);
-        if (r) return r;
-        p.tune = c;
-        r = build_synth_items(p);
-        if (!r && p.eq) {
-            p.eq->tune.valu = c.valu;
-            p.eq->tune.synth_mblock = c.synth_mblock;
-            r = build_synth_items(*p.eq);
+    const sht_tuning old = p.tune, old_eq = p.eq ? p.eq->tune : old;
+    SynthItems own, eq;
+    try {
+        rc = ensure_tables(p, t.valu);
+        if (!rc && p.eq) rc = ensure_tables(*p.eq, t.valu);
+        p.tune = t;
+        if (!rc) rc = make_synth_items(p, own);
+        if (!rc && p.eq) {
+            p.eq->tune.valu = t.valu;
+            p.eq->tune.synth_mblock = t.synth_mblock;
+            rc = make_synth_items(*p.eq, eq);
         }
-        return r;
-    };
-    if ((rc = apply(t))) (void)apply(old);
-    return rc;
+    } catch (const std::bad_alloc &) {
+        rc = no_memory();
+    }
+    if (rc) {
+        p.tune = old;
+        if (p.eq) p.eq->tune = old_eq;
+        return rc;
+    }
+    take_synth_items(p, own);
+    if (p.eq) take_synth_items(*p.eq, eq);
+    return SHT_OK;
 }
 
 LegView make_leg_view(const Plan &p)
@@ -554,7 +583,7 @@ extern "C" {
 
 int sht_plan_create(const sht_geom *g, int lmax, int mmax, int spin, int ntrans, int precision,
                     const sht_plan_opts *opts, sht_plan **out)
-{
+try {
     TraceRange tr("sht_plan_create");
     if (!out) { set_error("out is NULL"); return SHT_EINVAL; }
     *out = nullptr;
@@ -587,8 +616,8 @@ int sht_plan_create(const sht_geom *g, int lmax, int mmax, int spin, int ntrans,
     // set-up of the allocation-free entry point on this device (its failure
     // only disables that entry point)
     if (scratch_init(dev) != SHT_OK) set_error("");
-    Plan *p = new (std::nothrow) Plan();
-    if (!p) { set_error("host allocation failed"); return SHT_ENOMEM; }
+    std::unique_ptr<Plan> owner(new Plan());
+    Plan *p = owner.get();
     p->device = dev;
     p->lmax = lmax; p->mmax = mmax; p->spin = spin; p->ntrans = ntrans;
     p->precision = precision; p->ncomp = spin ? 2 : 1;
@@ -605,20 +634,27 @@ int sht_plan_create(const sht_geom *g, int lmax, int mmax, int spin, int ntrans,
         plan_free_device(p);
         rc = plan_build(*p, false);
     }
+    if (!rc) {
+        try {
+            p->serial = reg_add(p, H_PLAN);
+        } catch (const std::bad_alloc &) {
+            rc = no_memory();
+        }
+    }
     if (rc) {
         plan_free_device(p);
-        delete p;
         return rc;
     }
-    p->serial = reg_add(p, H_PLAN);
     log_msg(1,
             "plan %llu created on device %d: lmax %d, mmax %d, spin %d, %d transforms, %s, %d slots in %d tiles, "
             "%lld synthesis items; tuning synth_ncb=%d synth_mblock=%d anal_ncb=%d anal_tpw=%d valu=%d",
             (unsigned long long)p->serial, dev, lmax, mmax, spin, ntrans, precision == SHT_FP64 ? "fp64" : "fp32_mfma",
             p->nslots, p->ntiles, (long long)p->n_items, p->tune.synth_ncb, p->tune.synth_mblock, p->tune.anal_ncb,
             p->tune.anal_tpw, p->tune.valu);
-    *out = reinterpret_cast<sht_plan *>(p);
+    *out = reinterpret_cast<sht_plan *>(owner.release());
     return SHT_OK;
+} catch (const std::bad_alloc &) {
+    return no_memory();
 }
 
 void sht_plan_destroy(sht_plan *h)

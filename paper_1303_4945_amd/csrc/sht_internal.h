@@ -212,7 +212,6 @@ int launch_legendre_synth_spin(const Plan &p, const double *alm, double *phase, 
 int synth_spin_waves(const Plan &p);
 int synth0_ncb(const Plan &p);
 int anal0_batch_ncb(const Batch &b);
-int build_synth_items(Plan &p);
 // tuning: defaults for a plan, validity (SHT_OK or SHT_EUNSUPPORTED with a
 // message), and applying one (rebuilds the work lists, bumps the generation)
 sht_tuning default_tuning(const Plan &p);
