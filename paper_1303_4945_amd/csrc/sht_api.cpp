@@ -95,7 +95,7 @@ static void plan_free_device(Plan *p)
     fft_plan_free(p->fft);
     p->d_slot_cos = p->d_slot_sin = p->d_slot_chalf = p->d_slot_shalf = nullptr;
     p->d_slot_yn = p->d_slot_ys = nullptr;
-    p->d_coef = p->d_coef2 = nullptr; p->d_fl = nullptr; p->d_coef_ofs = nullptr; p->d_start = nullptr;
+    p->d_coef = nullptr; p->d_coef2 = nullptr; p->d_fl = nullptr; p->d_coef_ofs = nullptr; p->d_start = nullptr;
     p->d_tile_mlim = nullptr; p->d_synth_items = nullptr; p->d_anal_ms = nullptr;
     p->d_zeros = nullptr;
     p->d_dfac = nullptr;
@@ -235,6 +235,7 @@ static int split_slots(const Plan &p)
 
 int ensure_tables(Plan &p, bool valu)
 try {
+    const std::lock_guard<std::mutex> lk(p.tables_mu);
     const bool two = two_step(p) && !valu;
     if (two ? p.d_coef2 != nullptr : p.d_coef != nullptr) return SHT_OK;
     // the m that have an active slot
@@ -252,8 +253,13 @@ try {
         // theirs, is read but never used)
         const int64_t last = cofs.back();
         cofs.resize(p.mmax + 1, last);
-        if ((rc = dev_alloc((void **)&p.d_coef_ofs, cofs.size() * sizeof(int64_t), "coefficient table"))) return rc;
-        if ((rc = dev_upload(p.d_coef_ofs, cofs.data(), cofs.size() * sizeof(int64_t), "upload"))) return rc;
+        int64_t *o = nullptr;
+        if ((rc = dev_alloc((void **)&o, cofs.size() * sizeof(int64_t), "coefficient table"))) return rc;
+        if ((rc = dev_upload(o, cofs.data(), cofs.size() * sizeof(int64_t), "upload"))) {
+            dev_free(o);
+            return rc;
+        }
+        p.d_coef_ofs = o;
     }
     double4 *d = nullptr;
     double *f = nullptr;
@@ -269,8 +275,8 @@ try {
     if (two) {
         p.d_coef2 = d;
     } else {
-        p.d_coef = d;
         p.d_fl = f;
+        p.d_coef = d;
     }
     return SHT_OK;
 } catch (const std::bad_alloc &) {   // (of a host table: nothing is on the device yet)

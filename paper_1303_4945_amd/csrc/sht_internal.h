@@ -3,8 +3,10 @@
 
 #include <hip/hip_runtime.h>
 
+#include <atomic>
 #include <cstdint>
 #include <memory>
+#include <mutex>
 #include <string>
 #include <vector>
 
@@ -129,10 +131,14 @@ struct Plan {
     double *d_slot_cos = nullptr, *d_slot_sin = nullptr, *d_slot_chalf = nullptr,
            *d_slot_shalf = nullptr;
     int *d_slot_yn = nullptr, *d_slot_ys = nullptr;
-    double4 *d_coef = nullptr;       // with d_fl: one-step tables
-    double4 *d_coef2 = nullptr;      // two-step table (built where the kernels in use read it)
-    double *d_fl = nullptr;
-    int64_t *d_coef_ofs = nullptr;
+    // recursion tables: built where the kernels in use read them, at creation, retuning or
+    // the creation of a batch, which may come from several threads (tables_mu, held by
+    // ensure_tables) while another runs the plan (atomic)
+    std::mutex tables_mu;
+    std::atomic<double4 *> d_coef{nullptr};    // with d_fl: one-step tables
+    std::atomic<double4 *> d_coef2{nullptr};   // two-step table
+    std::atomic<double *> d_fl{nullptr};
+    std::atomic<int64_t *> d_coef_ofs{nullptr};
     StartCoef *d_start = nullptr;
     int *d_tile_mlim = nullptr;
     double *d_zeros = nullptr;
