@@ -354,13 +354,15 @@ int slot_mlim(const PlanShape &ps, const SlotHost &s)
     return -1;
 }
 
-// Fills tables of `total` entries, every m a chain of its own: fill(k, n) does the
-// m = k, k + n, ...  Large tables by several threads.  A failed allocation in any of
-// them is thrown here, after all have ended.
+// Fills tables that take `steps` (of 20 to 40 ns) in all, every m a chain of its own:
+// fill(k, n) does the m = k, k + n, ...  By up to 8 threads, each worth at least 16384
+// steps (starting one takes about 20 us).  A failed allocation in any of them is thrown
+// here, after all have ended.
 template <typename Fill>
-static void fill_by_m(int64_t total, Fill fill)
+static void fill_by_m(int64_t steps, Fill fill)
 {
-    const int nt = total < (1 << 18) ? 1 : (int)std::min(8u, std::max(1u, std::thread::hardware_concurrency()));
+    const int64_t most = std::min(8u, std::max(1u, std::thread::hardware_concurrency()));
+    const int nt = (int)std::max<int64_t>(1, std::min(most, steps >> 14));
     std::atomic<bool> failed{false};
     auto run = [&](int k) {
         try {
@@ -515,9 +517,13 @@ void build_start(const PlanShape &ps, std::vector<StartCoef> &st)
     const int s = ps.spin;
     st.assign((size_t)(ps.mmax + 1) * 2, StartCoef{});
     const long double inv4pi = 1.0L / (4.0L * 3.14159265358979323846264338327950288L);
-    for (int m = 0; m <= ps.mmax; ++m) {
+    auto fill_m = [&](int m) {
         const int l0 = std::max(m, s);
         for (int ch = 0; ch < 2; ++ch) {
+            if (ch && !s) {   // spin 0: one chain
+                st[(size_t)m * 2 + 1] = st[(size_t)m * 2];
+                continue;
+            }
             const int sig = (ch == 0) ? s : -s;
             int top, p_, q_, sign = (m & 1) ? -1 : 1;
             if (m >= s) {
@@ -563,7 +569,12 @@ void build_start(const PlanShape &ps, std::vector<StartCoef> &st)
             sc.pad = 0;
             st[(size_t)m * 2 + ch] = sc;
         }
-    }
+    };
+    // (a product of up to l0 ratios per chain)
+    const int64_t n = ps.mmax + 1;
+    fill_by_m(s ? n * n + 2 * n * s : n * n / 2, [&](int first, int step) {
+        for (int m = first; m <= ps.mmax; m += step) fill_m(m);
+    });
 }
 
 double count_triples(const PlanShape &ps, const std::vector<SlotHost> &slots, int slots_per_tile)

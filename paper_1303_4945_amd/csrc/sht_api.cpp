@@ -80,28 +80,25 @@ int dev_upload(void *dst, const void *src, size_t bytes, const char *what)
 
 static void plan_free_device(Plan *p)
 {
-    dev_free(p->d_slot_cos); dev_free(p->d_slot_sin);
-    dev_free(p->d_slot_chalf); dev_free(p->d_slot_shalf);
-    dev_free(p->d_slot_yn); dev_free(p->d_slot_ys);
+    dev_free(p->d_slot); dev_free(p->d_slot_ring);
     dev_free(p->d_coef); dev_free(p->d_coef2); dev_free(p->d_fl); dev_free(p->d_coef_ofs); dev_free(p->d_start);
     dev_free(p->d_tile_mlim); dev_free(p->d_synth_items); dev_free(p->d_anal_ms);
     dev_free(p->d_zeros);
     dev_free(p->d_dfac);
     dev_free(p->d_rh);
     dev_free(p->d_phase);
-    dev_free(p->d_slot_scale); dev_free(p->d_band); dev_free(p->d_band_alm);
+    dev_free(p->d_band); dev_free(p->d_band_alm);
     if (p->eq) plan_free_device(p->eq.get());
     p->eq.reset();
     fft_plan_free(p->fft);
-    p->d_slot_cos = p->d_slot_sin = p->d_slot_chalf = p->d_slot_shalf = nullptr;
-    p->d_slot_yn = p->d_slot_ys = nullptr;
+    p->d_slot = nullptr; p->d_slot_ring = nullptr;
     p->d_coef = nullptr; p->d_coef2 = nullptr; p->d_fl = nullptr; p->d_coef_ofs = nullptr; p->d_start = nullptr;
     p->d_tile_mlim = nullptr; p->d_synth_items = nullptr; p->d_anal_ms = nullptr;
     p->d_zeros = nullptr;
     p->d_dfac = nullptr;
     p->d_rh = nullptr;
     p->d_phase = nullptr;
-    p->d_slot_scale = nullptr; p->d_band = nullptr; p->d_band_alm = nullptr;
+    p->d_band = nullptr; p->d_band_alm = nullptr;
 }
 
 // Algorithmic work of the Legendre step (see sht.h): per kept (m, slot, l)
@@ -300,35 +297,27 @@ static int legendre_build(Plan &p, const std::vector<SlotHost> &slots, int first
         p.tile_mlim[t] = std::max(p.tile_mlim[t], slot_mlim(crit, slots[first + sl]));
         p.own_mlim = std::max(p.own_mlim, std::min(p.mmax, p.tile_mlim[t]));
     }
-    // slot tables (padded to whole tiles)
+    // slot tables (padded to whole tiles), doubles and ring numbers in one buffer each
     const int ns = p.ntiles * p.slots_per_tile;
-    std::vector<double> sc(ns, 0.0), ss(ns, 0.0), sch(ns, 1.0), ssh(ns, 0.0), scale(3 * ns, 0.0);
-    std::fill(scale.begin(), scale.begin() + ns, 1.0);
-    std::vector<int> yn(ns, -1), ys(ns, -1);
+    std::vector<double> tab((size_t)7 * ns, 0.0);
+    double *sc = tab.data(), *ss = sc + ns, *sch = ss + ns, *ssh = sch + ns, *scale = ssh + ns;
+    std::fill(sch, sch + ns, 1.0);
+    std::fill(scale, scale + ns, 1.0);
+    std::vector<int> ring((size_t)2 * ns, -1);
     for (int i = 0; i < p.nslots; ++i) {
         const SlotHost &s = slots[first + i];
         sc[i] = s.cth; ss[i] = s.sth;
         sch[i] = s.chalf; ssh[i] = s.shalf;
-        yn[i] = s.yn; ys[i] = s.ys;
+        ring[i] = s.yn; ring[ns + i] = s.ys;
         // the phases of a scalar part: over sin^s t (0: crit_spin is the plan's own spin)
         for (int k = p.spin; k < p.crit_spin; ++k) scale[i] /= s.sth;
         scale[ns + i] = s.c2;
         scale[2 * ns + i] = s.s2;
     }
-    if ((rc = dev_alloc((void **)&p.d_slot_cos, ns * sizeof(double), "slot tables"))) return rc;
-    if ((rc = dev_alloc((void **)&p.d_slot_sin, ns * sizeof(double), "slot tables"))) return rc;
-    if ((rc = dev_alloc((void **)&p.d_slot_chalf, ns * sizeof(double), "slot tables"))) return rc;
-    if ((rc = dev_alloc((void **)&p.d_slot_shalf, ns * sizeof(double), "slot tables"))) return rc;
-    if ((rc = dev_alloc((void **)&p.d_slot_scale, scale.size() * sizeof(double), "slot tables"))) return rc;
-    if ((rc = dev_alloc((void **)&p.d_slot_yn, ns * sizeof(int), "slot tables"))) return rc;
-    if ((rc = dev_alloc((void **)&p.d_slot_ys, ns * sizeof(int), "slot tables"))) return rc;
-    if ((rc = dev_upload(p.d_slot_cos, sc.data(), ns * sizeof(double), "upload"))) return rc;
-    if ((rc = dev_upload(p.d_slot_sin, ss.data(), ns * sizeof(double), "upload"))) return rc;
-    if ((rc = dev_upload(p.d_slot_chalf, sch.data(), ns * sizeof(double), "upload"))) return rc;
-    if ((rc = dev_upload(p.d_slot_shalf, ssh.data(), ns * sizeof(double), "upload"))) return rc;
-    if ((rc = dev_upload(p.d_slot_scale, scale.data(), scale.size() * sizeof(double), "upload"))) return rc;
-    if ((rc = dev_upload(p.d_slot_yn, yn.data(), ns * sizeof(int), "upload"))) return rc;
-    if ((rc = dev_upload(p.d_slot_ys, ys.data(), ns * sizeof(int), "upload"))) return rc;
+    if ((rc = dev_alloc((void **)&p.d_slot, tab.size() * sizeof(double), "slot tables"))) return rc;
+    if ((rc = dev_alloc((void **)&p.d_slot_ring, ring.size() * sizeof(int), "slot tables"))) return rc;
+    if ((rc = dev_upload(p.d_slot, tab.data(), tab.size() * sizeof(double), "upload"))) return rc;
+    if ((rc = dev_upload(p.d_slot_ring, ring.data(), ring.size() * sizeof(int), "upload"))) return rc;
 
     p.tune = default_tuning(p);
     if ((rc = ensure_tables(p, p.tune.valu))) return rc;
@@ -506,17 +495,16 @@ LegView make_leg_view(const Plan &p)
     v.rescale_bits = p.rescale_bits;
     v.thresh_bits = p.rescale_bits / 2;
     v.polar_T = p.polar_T;
-    v.slot_cos = p.d_slot_cos; v.slot_sin = p.d_slot_sin;
-    v.slot_chalf = p.d_slot_chalf; v.slot_shalf = p.d_slot_shalf;
-    v.slot_yn = p.d_slot_yn; v.slot_ys = p.d_slot_ys;
+    const int64_t ns = (int64_t)p.ntiles * p.slots_per_tile;
+    v.slot_cos = p.d_slot; v.slot_sin = p.d_slot + ns;
+    v.slot_chalf = p.d_slot + 2 * ns; v.slot_shalf = p.d_slot + 3 * ns;
+    v.slot_scale = p.d_slot + 4 * ns;
+    v.slot_c2 = p.d_slot + 5 * ns; v.slot_s2 = p.d_slot + 6 * ns;
+    v.slot_yn = p.d_slot_ring; v.slot_ys = p.d_slot_ring + ns;
     v.coef = p.d_coef; v.coef2 = p.d_coef2; v.fl = p.d_fl; v.coef_ofs = p.d_coef_ofs; v.start = p.d_start;
     v.tile_mlim = p.d_tile_mlim;
     v.zeros = p.d_zeros;
     v.dfac = p.d_dfac;
-    const int64_t ns = (int64_t)p.ntiles * p.slots_per_tile;
-    v.slot_scale = p.d_slot_scale;
-    v.slot_c2 = p.d_slot_scale + ns;
-    v.slot_s2 = p.d_slot_scale + 2 * ns;
     v.crit_spin = p.crit_spin;
     v.crit_lmax = p.crit_lmax;
     v.nalm = p.nalm;
@@ -779,12 +767,11 @@ int sht_plan_info(const sht_plan *h, int64_t *n_items, int64_t *device_bytes)
         const Plan *e = p->eq.get();
         const Plan none;
         if (!e) e = &none;
-        const void *bufs[] = {p->d_coef2, e->d_coef2, p->d_slot_scale, p->d_band, p->d_band_alm, e->d_slot_cos, e->d_slot_sin, e->d_slot_chalf,
-                              e->d_slot_shalf, e->d_slot_scale, e->d_slot_yn, e->d_slot_ys, e->d_coef, e->d_fl,
+        const void *bufs[] = {p->d_band, p->d_band_alm, e->d_slot, e->d_slot_ring, e->d_coef, e->d_coef2, e->d_fl,
                               e->d_coef_ofs, e->d_start, e->d_tile_mlim, e->d_zeros, e->d_dfac, e->d_synth_items,
-                              e->d_anal_ms, p->d_slot_cos, p->d_slot_sin, p->d_slot_chalf, p->d_slot_shalf, p->d_slot_yn,
-                              p->d_slot_ys, p->d_coef, p->d_fl, p->d_coef_ofs, p->d_start, p->d_tile_mlim,
-                              p->d_zeros, p->d_dfac, p->d_synth_items, p->d_anal_ms, p->d_phase, p->d_rh,
+                              e->d_anal_ms, p->d_slot, p->d_slot_ring, p->d_coef, p->d_coef2, p->d_fl,
+                              p->d_coef_ofs, p->d_start, p->d_tile_mlim, p->d_zeros, p->d_dfac, p->d_synth_items,
+                              p->d_anal_ms, p->d_phase, p->d_rh,
                               p->fft.d_rows, p->fft.d_tw, p->fft.d_perm, p->fft.d_blue, p->fft.d_mvalid,
                               p->fft.d_phase_rot};
         int64_t total = 0;

@@ -120,7 +120,6 @@ struct Plan {
     std::unique_ptr<Plan> eq;
     double *d_band_alm = nullptr;
     BandL *d_band = nullptr;
-    double *d_slot_scale = nullptr;  // per slot: [0, n) factor, [n, 2 n) cos^2 t, [2 n, 3 n) sin^2 t (n padded)
     int own_mlim = -1;               // largest m with an active slot among the plan's own
     std::vector<int> tile_mlim;
     // host-side work lists
@@ -128,9 +127,10 @@ struct Plan {
     sht_tuning tune{};               // launch shapes (synthesis column blocks, m blocks, ...)
     std::vector<int> anal_ms;
     // device memory
-    double *d_slot_cos = nullptr, *d_slot_sin = nullptr, *d_slot_chalf = nullptr,
-           *d_slot_shalf = nullptr;
-    int *d_slot_yn = nullptr, *d_slot_ys = nullptr;
+    // per slot, n = ntiles slots_per_tile of each: cos t, sin t, cos t/2, sin t/2, factor,
+    // cos^2 t, sin^2 t; ring at t, ring at pi - t
+    double *d_slot = nullptr;
+    int *d_slot_ring = nullptr;
     // recursion tables: built where the kernels in use read them, at creation, retuning or
     // the creation of a batch, which may come from several threads (tables_mu, held by
     // ensure_tables) while another runs the plan (atomic)

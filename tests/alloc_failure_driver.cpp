@@ -142,6 +142,20 @@ int main()
         drop();
         return ok;
     });
+    std::vector<sht::StartCoef> sref, st;
+    ps.spin = 2;
+    sht::build_start(ps, sref);
+    each("start values", [&] {
+        bool ok = true;
+        try {
+            sht::build_start(ps, st);
+            if (!same(st, sref)) ++g_bad;
+        } catch (const std::bad_alloc &) {
+            ok = false;
+        }
+        std::vector<sht::StartCoef>().swap(st);
+        return ok;
+    });
     std::printf(g_bad ? "FAILED\n" : "all checks passed\n");
     return g_bad ? 1 : 0;
 }
