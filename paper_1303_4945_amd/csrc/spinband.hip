@@ -118,9 +118,10 @@ __device__ __forceinline__ void band_weights(const BandL *__restrict__ b, int l,
 }
 
 // values a, x at the five degree offsets -> -(W a + i X x), the first component
-// of either direction, or (SECOND) -(W a - i X x), the second (c: -W and X)
+// of either direction, or (SECOND) -(W a - i X x), the second (c: -W and X).  m = 0: X
+// is 0 and the imaginary parts are never used; 0 x takes an Inf or NaN of x along.
 template <int S, bool SECOND>
-__device__ __forceinline__ double2 band_apply(const double (&c)[5], const double2 (&a)[5], const double2 (&x)[5])
+__device__ __forceinline__ double2 band_apply(const double (&c)[5], const double2 (&a)[5], const double2 (&x)[5], int m)
 {
     double2 o = make_double2(0.0, 0.0);
 #pragma unroll
@@ -131,7 +132,7 @@ __device__ __forceinline__ double2 band_apply(const double (&c)[5], const double
             o.x = fma(c[i], a[i].x, o.x);
             o.y = fma(c[i], a[i].y, o.y);
         } else {
-            o.x = fma(SECOND ? -c[i] : c[i], x[i].y, o.x);
+            o.x = fma(SECOND ? -c[i] : c[i], m ? x[i].y : x[i].x, o.x);
             o.y = fma(SECOND ? c[i] : -c[i], x[i].x, o.y);
         }
     }
@@ -176,8 +177,8 @@ __global__ __launch_bounds__(256) void k_band_synth(const double2 *__restrict__ 
             e[i] = ok[i] ? make_double2(ev.x, m ? ev.y : 0.0) : make_double2(0.0, 0.0);
             bb[i] = ok[i] ? make_double2(bv.x, m ? bv.y : 0.0) : make_double2(0.0, 0.0);
         }
-        q[(int64_t)t * 2 * nalm_q + dst] = band_apply<S, false>(c, e, bb);
-        q[((int64_t)t * 2 + 1) * nalm_q + dst] = band_apply<S, true>(c, bb, e);
+        q[(int64_t)t * 2 * nalm_q + dst] = band_apply<S, false>(c, e, bb, m);
+        q[((int64_t)t * 2 + 1) * nalm_q + dst] = band_apply<S, true>(c, bb, e, m);
     }
 }
 
@@ -225,13 +226,13 @@ __global__ __launch_bounds__(256) void k_band_anal(const double2 *__restrict__ q
             su[i] = ok[i] ? uv : make_double2(0.0, 0.0);
         }
         double2 *oe = alm + (int64_t)t * ncout * nalm + dst;
-        double2 v = band_apply<S, false>(c, sq, su);
+        double2 v = band_apply<S, false>(c, sq, su, m);
         if (m == 0) v.y = 0.0;
         if (add) v = make_double2(oe->x + v.x, oe->y + v.y);
         *oe = v;
         if (deriv) continue;
         oe += nalm;
-        v = band_apply<S, true>(c, su, sq);
+        v = band_apply<S, true>(c, su, sq, m);
         if (m == 0) v.y = 0.0;
         if (add) v = make_double2(oe->x + v.x, oe->y + v.y);
         *oe = v;
