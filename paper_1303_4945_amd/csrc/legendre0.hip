@@ -691,7 +691,9 @@ static void launch_anal0_t(const Plan &p, const LegView &v, const double *phase,
 int launch_legendre_anal0(const Plan &p, const double *phase, double *alm, int mode, hipStream_t s)
 {
     const LegView v = make_leg_view(p);
-    switch (anal0_ncb(p)) {
+    const int ncb = anal0_ncb(p);
+    log_msg(3, "two-step Legendre analysis plan %llu: %d column blocks", (unsigned long long)p.serial, ncb);
+    switch (ncb) {
     case 4: launch_anal0_t<4>(p, v, phase, alm, mode, s); break;
     case 2: launch_anal0_t<2>(p, v, phase, alm, mode, s); break;
     default: launch_anal0_t<1>(p, v, phase, alm, mode, s); break;
