@@ -351,7 +351,6 @@ __device__ __forceinline__ void synth_item(const LegView &v, const WaveItem it,
 
     // ring indices of this lane's output rows, all loaded before any store
     int eyn[NSB][4], eys[NSB][4];
-    double escale[SPIN ? 1 : NSB][4];
 #pragma unroll
     for (int sb = 0; sb < NSB; ++sb)
 #pragma unroll
@@ -359,7 +358,6 @@ __device__ __forceinline__ void synth_item(const LegView &v, const WaveItem it,
             const int slot = tile * SPT + sb * 16 + c_row<F32>(lane, r);   // < ntiles * SPT
             eyn[sb][r] = v.slot_yn[slot];
             eys[sb][r] = v.slot_ys[slot];
-            if constexpr (SPIN == 0) escale[sb][r] = v.slot_scale[slot];
         }
 
     // epilogue: ring t = A0 + A1, ring pi - t = sigma (A0 - A1), both times tau_o
@@ -386,7 +384,7 @@ __device__ __forceinline__ void synth_item(const LegView &v, const WaveItem it,
                 const int comp = SPIN ? (o >> 1) : 0, reim = o & 1;
                 const int yn = eyn[sb][r], ys = eys[sb][r];
                 const int64_t rowbase = ((int64_t)t * NCOMP + comp) * v.nrings;
-                const double ts = SPIN ? (tneg ? -1.0 : 1.0) : escale[sb][r];   // undo tau_o; slot factor
+                const double ts = tneg ? -1.0 : 1.0;   // undo tau_o
                 if (yn >= 0) phase[((rowbase + yn) * (v.mmax + 1) + m) * 2 + reim] = ts * (c0 + c1);
                 if (ys >= 0) phase[((rowbase + ys) * (v.mmax + 1) + m) * 2 + reim] = (ssign * ts) * (c0 - c1);
             }
@@ -587,11 +585,9 @@ __device__ __forceinline__ void anal_item(const LegView &v, const int m, const i
             const bool active = ptile[i] >= 0;
             const int slot0 = active ? ptile[i] * SPT : 0;
             int ynv[KSA], ysv[KSA];
-            double scv[SPIN ? 1 : KSA];
 #pragma unroll
             for (int ks = 0; ks < KSA; ++ks) {
                 const int slot = slot0 + 4 * ks + kk;     // < ntiles * SPT (tables padded)
-                if constexpr (SPIN == 0) scv[ks] = v.slot_scale[slot];
                 const int yn = v.slot_yn[slot], ys = v.slot_ys[slot];
                 const bool ok = active && slot < v.nslots;
                 ynv[ks] = ok ? yn : -1;
@@ -612,7 +608,7 @@ __device__ __forceinline__ void anal_item(const LegView &v, const int m, const i
                     const double gs0 = phase[((rowbase + (ys >= 0 ? ys : 0)) * (v.mmax + 1) + m) * 2 + reim];
                     const double gn = (tok && yn >= 0) ? gn0 : 0.0;
                     const double gs = (tok && ys >= 0) ? ssign * gs0 : 0.0;
-                    const double sg = SPIN ? ((o == 3) ? 1.0 : -1.0) : scv[SPIN ? 0 : ks];   // -tau_o (spin > 0)
+                    const double sg = SPIN ? ((o == 3) ? 1.0 : -1.0) : 1.0;   // -tau_o (spin > 0)
                     gw[i][0][ks][cb] = (T)(sg * (gn + gs));
                     gw[i][1][ks][cb] = (T)(sg * (gn - gs));
                     nonfin = nonfin || not_finite(gw[i][0][ks][cb]) || not_finite(gw[i][1][ks][cb]);
