@@ -405,9 +405,11 @@ int time_launches(F fn, int reps, double &ms)
 
 std::string tune_key(const Plan &p)
 {
+    // (a plan with a scalar part runs other kernels than the timings of a file from
+    // before it had one were taken with)
     char buf[256];
-    std::snprintf(buf, sizeof buf, "sht-tuning gfx950 lmax=%d mmax=%d spin=%d ntrans=%d nrings=%d prec=%d",
-                  p.lmax, p.mmax, p.spin, p.ntrans, p.geom.nrings, p.precision);
+    std::snprintf(buf, sizeof buf, "sht-tuning gfx950 lmax=%d mmax=%d spin=%d ntrans=%d nrings=%d prec=%d%s",
+                  p.lmax, p.mmax, p.spin, p.ntrans, p.geom.nrings, p.precision, p.eq ? " scalar-part" : "");
     return buf;
 }
 
