@@ -191,7 +191,9 @@ int sht_execute(sht_plan *p, int direction, const double *in, double *out,
    real_harmonics, its coefficient workspace) is replaced by a static device
    array of the library of 64 MiB per device (sht_noalloc_capacity), which each
    device holds from the first plan creation on it until the process ends.
-   The call allocates nothing.  SHT_EINVAL when the plan needs more workspace
+   The call allocates nothing; the coefficient workspace that plans of spins 1 and 2
+   have from some size on (see above) stays the plan's own.  SHT_EINVAL when the plan
+   needs more workspace
    than that (ntrans * ncomp * nrings * (mmax + 1) * 16 bytes of phases, plus
    ntrans * ncomp * nalm * 16 with real_harmonics).  Every call on one device
    shares that device's array: calls that overlap in time on one device (on
@@ -224,7 +226,8 @@ int sht_ring_fft(sht_plan *p, int direction, const double *in, double *out,
    the synthesis).  With K the kept (m, ring slot, degree) triples (Sect. 3.3),
    J = ntrans, and per triple r = 4 (spin 0) or 10 (spin s > 0: two chains,
    Sect. 4.1) flops of recursion and c = 4 or 16 flops of products per
-   transform:
+   transform (ring slots that a spin-1 or spin-2 FP64 plan computes as spin-0 sums:
+   r = 4, c = 8):
      flops_fp64  = K r + K J c for SHT_FP64 (recursion on the vector units,
                    products on FP64 matrix cores), K r for SHT_FP32_MFMA;
      flops_mfma  = K J c for SHT_FP32_MFMA (FP32 matrix-core products), 0 for

@@ -104,13 +104,15 @@ static void plan_free_device(Plan *p)
 // Algorithmic work of the Legendre step (see sht.h): per kept (m, slot, l)
 // triple the recursion (4 flops for spin 0: two FMAs; 10 for spin s > 0: two
 // chains of 5, Sect. 4.1) plus per transform and ring of the slot 4 (spin 0) /
-// 16 (spin s > 0) flops of products; HBM: a_lm + 2 x phases + maps.
+// 16 (spin s > 0) flops of products; the slots of a scalar part as spin 0, two sums
+// per transform.  HBM: a_lm + 2 x phases + maps.
 static void count_work(Plan &p)
 {
-    const double triples = count_triples(p.shape(), p.slots, p.spin ? 32 : 64);
-    const double r = p.spin ? 10.0 : 4.0, c = p.spin ? 16.0 : 4.0;
-    p.flops_rec = triples * r;
-    p.flops_prod = triples * c * p.ntrans;
+    const auto split = p.slots.begin() + p.nslots;
+    const std::vector<SlotHost> own(p.slots.begin(), split), scalar(split, p.slots.end());
+    const double k = count_triples(p.shape(), own, p.slots_per_tile), kq = count_triples(p.shape(), scalar, 64);
+    p.flops_rec = k * (p.spin ? 10.0 : 4.0) + kq * 4.0;
+    p.flops_prod = (k * (p.spin ? 16.0 : 4.0) + kq * 8.0) * p.ntrans;
     double alm_b = (double)p.ntrans * p.ncomp * p.nalm * 16.0;
     double ph_b = (double)p.ntrans * p.ncomp * p.geom.nrings * (p.mmax + 1) * 16.0;
     double map_b = (double)p.ntrans * p.ncomp * p.geom.npix * 8.0;
