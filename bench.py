@@ -46,7 +46,8 @@ METRIC = "alm2map+map2alm pairs/sec at lmax=4095; FP32-MFMA vs FP64 speedup at 1
 # kernel sources hash to what they were when the counters were taken.
 TRAFFIC_PROFILE = os.path.join(ROOT, "profiles", "legendre_anal_gl4095s2_hbm_traffic.md")
 KERNEL_SOURCES = [os.path.join(ROOT, "paper_1303_4945_amd", "csrc", f)
-                  for f in ("legendre.hip", "sht_internal.h")] + \
+                  for f in ("legendre.hip", "legendre0.hip", "legendre_dev.h", "spinband.hip",
+                            "sht_api.cpp", "sht_internal.h")] + \
                  [os.path.join(ROOT, "paper_1303_4945_amd", "build.py")]
 
 

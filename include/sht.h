@@ -255,8 +255,9 @@ int sht_memory_stats(int64_t *live_buffers, int64_t *live_bytes);
    one direction per call) as one stream-ordered unit (Sect. 3.2's simultaneous
    transforms, with mixed band limits and grids): the Legendre analyses of
    every plan are merged into one persistent launch over a queue of items
-   popped by an atomic counter (plans tuned to the vector path run their own
-   analysis launches instead); the Legendre syntheses (each plan's die-aware
+   popped by an atomic counter (a batch with a plan on the vector path, or with one of
+   spin 1 or 2 that runs part of its rings as spin-0 sums, runs every plan's own analysis
+   launches instead); the Legendre syntheses (each plan's die-aware
    item list) and the ring FFTs run per plan, on concurrent streams; on a
    non-null stream the whole sequence is captured once into a HIP graph and
    replayed (captured again when the buffers, the stream or the tuning of a
@@ -287,8 +288,9 @@ int sht_batch_legendre(sht_batch *b, int direction, const double *const *in,
                 the ring FFTs, while the Legendre syntheses of all plans run as
                 one persistent launch over one queue of (plan, m, slot tile,
                 transform group) items in the queue order (needs every plan on
-                the matrix-core kernels with the same synthesis column blocks
-                and carry interval, else the plans' own launches run).
+                the matrix-core kernels alone, with the same synthesis column
+                blocks (spin 0 in FP64: any) and carry interval, else the plans'
+                own launches run).
    Defaults: SHT_QUEUE_COST, concurrent 1.  Results do not depend on either.
    SHT_EINVAL for other values. */
 enum { SHT_QUEUE_COST = 0, SHT_QUEUE_MPAIRS = 1 };
@@ -321,7 +323,7 @@ int sht_plan_set_tuning(sht_plan *p, const sht_tuning *t);
 /* Pick the tuning of a plan by timing the candidate combinations on scratch
    data (one Legendre synthesis and analysis each) for about budget_seconds;
    results are cached in the text file named by $SHT_TUNE_CACHE (if set), one
-   line per plan shape, so that a later plan of the same shape takes the cached
+   line per plan shape and kind of kernels, so that a later plan of the same shape takes the cached
    choice without timing (budget 0: only the cache is consulted).  Batches that
    hold the plan capture their launches again at their next execution. */
 int sht_autotune(sht_plan *p, double budget_seconds);

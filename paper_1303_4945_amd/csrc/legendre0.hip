@@ -148,7 +148,8 @@ __device__ __forceinline__ double4 chain2_coef(const double4 q) { return double4
 // transforms at lmax 4095 (32 scalar ones, 88% of the slots): 44.7 ms in the
 // one-step kernel of 64 slots x 16 columns, 31.5 here; recursion of chunk c + 1
 // interleaved with the products of chunk c and half the wavefronts per SIMD 32.5; 64
-// columns per wavefront 32.1.  The recursion's few instructions run at raised
+// columns per wavefront 32.1.  (In the whole transform, 86% of the slots: 33.7 ms, matrix
+// cores busy 0.58 of the cycles; 0.44 with one column block.)  The recursion's few instructions run at raised
 // priority: beside another wavefront's matrix instructions each of them waits for
 // one to end (72 cycles; 137 at equal priority).
 constexpr int S0_LC = 16;
@@ -329,7 +330,9 @@ __global__ __launch_bounds__(64 * NW, 4) void k_legendre_synth0(LegView v, const
 // transforms at lmax 4095 (64 scalar columns): 42.2 ms in the one-step kernel of 64
 // slots x 16 columns on the same slots, 39.2 here; a chunk takes 13.3-14.6k cycles, of
 // which 8.8k are matrix instructions at their issue rate, 2.0-2.6k the recursion,
-// 1.6k the sums into a_lm.  The recursion of chunk c + 1 interleaved with the
+// 1.6k the sums into a_lm.  (In the whole transform: 43.4 ms, matrix cores busy 0.46 of
+// the cycles, partly filled passes and the ends of the launch included; 0.41 with one
+// column block.)  The recursion of chunk c + 1 interleaved with the
 // products of chunk c (two buffers of lambda) was no faster, two groups of 32 columns
 // 7% slower.
 constexpr int A0_LC = 32;

@@ -696,8 +696,10 @@ __device__ __forceinline__ double2 fold_bin_single(const FftView &fv, const doub
 // the bins of a second ring.  A short ring has few bins and many terms (a HEALPix
 // polar ring of 4 pixels folds 2 mv / 4 of them onto each, mv >= 100): one thread per
 // bin, each term a dependent load, took 68 us of the 343 us pair of one spin-2
-// transform at N_side 128, this takes 17.  Up to 128 bins: there 1024 threads give
-// each at least 8 terms at a time; longer rings have fewer terms per bin than lanes.
+// transform at N_side 128, this takes 17.  Such rings run in work groups of 256 threads,
+// 2 per bin at 128 bins.  Ring synthesis with a limit of 16 / 64 / 128 / 256 bins: 8
+// transforms at N_side 128 86 / 71 / 68 / 62-72 us, one at N_side 512 119 / 109 / 108 /
+// 104, at N_side 1024 217 / 206 / 206 / 203; 128 keeps the buffer at 2 KB.
 constexpr int FOLD_MAX = 128;
 
 __device__ __forceinline__ void fold_short(const FftView &fv, double2 *bins, const double2 *Fa, int ya, int mva,

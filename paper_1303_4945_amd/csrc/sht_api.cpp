@@ -347,9 +347,10 @@ static int legendre_build(Plan &p, const std::vector<SlotHost> &slots, int first
 // m values of the analysis launch, 0 .. top, in the order of its work groups:
 // longest degree ranges (small m) first.  Spin 0 in FP64: work group i runs on die i
 // mod NUM_XCD, so within 64 m the die's eight groups take eight consecutive m, whose
-// phases share 128-byte lines, and a line is read into one die's L2 once (32
-// transforms at lmax 4095: 64 -> 28 GB read per launch, 40.0 -> 39.2 ms; the other
-// kernels, whose lines meet in another order, lost 2%).
+// phases share 128-byte lines, and a line is read into one die's L2 once.  In order of m /
+// so: 32 transforms at lmax 4095 73.8 / 48.1 GB read per launch (counter calibrated by a
+// copy), 44.9 / 45.3 ms; 16 at lmax 2047 3.63 / 3.56 ms, 64 at lmax 1023 2.25 / 2.10, 5 at
+// lmax 777 173 / 165 us.  The other kernels, whose lines meet in another order, lost 2%.
 static int anal_list_build(Plan &p, int top)
 {
     p.anal_ms.resize(top + 1);

@@ -260,7 +260,7 @@ int launch_ring_anal(const Plan &p, const double *map, double *phase, bool use_w
 int launch_phase_tail_zero(const Plan &p, double *phase, hipStream_t s);
 
 // scalar part of spin-1 and spin-2 plans (spinband.hip): per-degree factors of
-// the band (host table of lmax + 2 spin + 2 entries), and the banded maps between
+// the band (device table of lmax + 2 spin + 3 entries), and the banded maps between
 // the plan's coefficients and the scalar part's
 int band_upload(Plan &p);
 int launch_band_synth(const Plan &p, const double *alm, double *q, bool deriv, hipStream_t s);
