@@ -952,6 +952,11 @@ __device__ __forceinline__ void chains_chunk(Chain (&c)[K], bool &slow, int l0, 
     slow = wave_any(any);
 }
 
+// slots per lane of one form: one, of four two (five routines instead of three: one spin-2
+// transform at lmax 4095 analysis 8.75 -> 8.91 ms, at lmax 1700 1.04 -> 1.10)
+template <int K>
+constexpr int form_slots() { return K > 2 ? 2 : 1; }
+
 // Chains of the K slots of this lane (tile[k] < 0: none), the number of slots in
 // difference form (EACH: the first ones, up to the last 64 of the wavefront with one
 // close to a pole; otherwise all or none) and the scale flag.
@@ -965,7 +970,7 @@ __device__ __forceinline__ void chains_init(const LegView &v, int m, const int (
     for (int k = 0; k < K * NCH; ++k) {
         const int kt = k / NCH;
         c[k] = chain_init(v, m, tile[kt] >= 0 ? tile[kt] * 64 + lane : v.nslots, k % NCH);
-        if (wave_any(c[k].x > DIFF_FORM_COS)) ndiff = EACH ? kt + 1 : K;
+        if (wave_any(c[k].x > DIFF_FORM_COS)) ndiff = EACH ? (kt / form_slots<K>() + 1) * form_slots<K>() : K;
         s = s || c[k].k < 0;
     }
     slow = wave_any(s);
@@ -985,11 +990,7 @@ __device__ __forceinline__ void by_form(int ndiff, Run run)
 {
     if (ndiff == 0) return run(std::integral_constant<int, 0>{});
     if constexpr (EACH && K > 1)
-        if (ndiff == 1) return run(std::integral_constant<int, 1>{});
-    if constexpr (EACH && K > 2)
-        if (ndiff == 2) return run(std::integral_constant<int, 2>{});
-    if constexpr (EACH && K > 3)
-        if (ndiff == 3) return run(std::integral_constant<int, 3>{});
+        if (ndiff == K / 2) return run(std::integral_constant<int, K / 2>{});
     run(std::integral_constant<int, K>{});
 }
 

@@ -194,13 +194,15 @@ static int build_synth_items(Plan &p)
 // units of the last place (spin 2), beside the recursion's own error, which grows with
 // lmax.  Relative rms error of phases, scalar part over spin kernels (C_l = 1/(l + 1)^2,
 // the larger of vector and matrix kernels, 80 rings in the band of 0.05 with the line):
-// spin 2, lmax 40 1.04, 80 1.09, 130 1.08, 200 1.07, 383 1.10, 1279 1.13; spin 1, 40 1.05,
-// 80 1.10, 130 1.05, 200 1.07.  At sin t = 0.20-0.25 instead: 3.3, 2.6, 2.6, 2.2, 1.5, 1.1;
-// spin 1, 1.9, 1.3, 1.2, 1.1.  From lmax 1700 on 0.2: the error is the recursion's there
-// down to that line, and nearer the poles the split saves little.
+// spin 2, lmax 40 1.04, 80 1.09, 130 1.08, 200 1.07, 383 1.10, 1279 1.13, 2047 1.10, 4095
+// 1.06; spin 1, 40 1.05, 80 1.10, 130 1.05, 200 1.07, 2047 1.00.  At sin t = 0.20-0.25
+// instead: lmax 40 3.3, 80 2.6, 130 2.6, 200 2.2, 383 1.5; spin 1, 1.9, 1.3, 1.2, 1.1.
+// From lmax 2000 on 0.19, though the error would allow less: 16 transforms at lmax 4095
+// take 106.4 ms with 256 slots below it, 108.5 with 224 (0.15), whose others fill an
+// eighth pass of the analysis in part.
 static double split_sin(const Plan &p)
 {
-    return std::max(0.2, (p.spin == 1 ? 1.7 : 2.4) / std::cbrt((double)p.lmax));
+    return std::max(0.19, (p.spin == 1 ? 1.7 : 2.4) / std::cbrt((double)p.lmax));
 }
 
 // A scalar part costs four more launches on the matrix cores (two on the vector
